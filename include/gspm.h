@@ -194,10 +194,11 @@ typedef struct {
                                previous displacement increment (0 if unused) */
     int64_t ms_iters;       /* local_demag: magnetostatic CG iterations (GSPM_MIXED: inner FP32), summed */
     int64_t mech_refinements; /* GSPM_MIXED: the refinements of the elastic solves (part of `refinements`) */
-    double gs_matvec_ms;    /* profile mode: summed kernel duration of the working GS CG iteration launches on
-                               three components (one fused launch per iteration: the matvec with the CG vector
-                               updates; stages 1 and 3; those after convergence excluded) */
-    int64_t gs_matvec_launches; /* profile mode: their number */
+    double gs_matvec_ms;    /* profile mode: summed duration of the GS CG iterations on three components (stages 1
+                               and 3).  Solves that run in one launch count that launch whole (residuals and
+                               refinements included); meshes too large for that count the fused launches of the
+                               iterations, those after convergence excluded */
+    int64_t gs_matvec_launches; /* profile mode: the number of those iterations */
     double phase_ms[8];     /* profile mode: device time of each phase of Alg. B.1, summed over the steps:
                                [0] averages at m^n, [1] elastic solve (right-hand side, start, CG), [2] local
                                magnetostatic solve, [3] GS stage 1 (field right-hand side, 3 solves), [4] stage 2

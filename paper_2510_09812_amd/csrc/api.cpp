@@ -217,6 +217,7 @@ gspm_ctx::~gspm_ctx() {
     if (h_flags) hipHostFree(h_flags);
     if (h_mixed) hipHostFree(h_mixed);
     if (h_step) hipHostFree(h_step);
+    if (h_res) hipHostFree(h_res);
     if (own_stream && stream) hipStreamDestroy(stream);
 }
 
@@ -244,6 +245,10 @@ void gspm_ctx::release_mesh() {
     dev_free(this, b.det_part); dev_free(this, b.det_dst); dev_free(this, b.det_count); dev_free(this, b.inc_ptr);
     dev_free(this, b.inc_ent);
     dev_free(this, b.gs_halo_ptr); dev_free(this, b.gs_halo_ids);
+    dev_free(this, b.res_col); dev_free(this, b.res_halo_ptr); dev_free(this, b.res_halo_ids); dev_free(this, b.res_slot);
+    dev_free(this, b.res_xq); dev_free(this, b.res_slots); dev_free(this, b.res_epoch);
+    res_gs = gspm::ResLayout{};
+    res_off = false;
     dev_free(this, b.gs_off); dev_free(this, b.gs_col); dev_free(this, b.gs_kv); dev_free(this, b.gs_mv);
     dev_free(this, b.gs_kd); dev_free(this, b.gs_md);
     for (int k = 0; k < 2; ++k) {
@@ -343,6 +348,8 @@ gspm_status gspm_create(gspm_ctx **out, const gspm_create_opts *opts) {
                              hipHostMallocCoherent) == hipSuccess;
     ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_step), sizeof(double) * 16, hipHostMallocCoherent) ==
                    hipSuccess;
+    ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_res), sizeof(ResResult), hipHostMallocCoherent) ==
+                   hipSuccess;
     for (auto &e : c->ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreate(&c->t0) == hipSuccess && hipEventCreate(&c->t1) == hipSuccess;
     for (auto &e : c->phase_ev) ok = ok && hipEventCreate(&e) == hipSuccess;
@@ -408,6 +415,15 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
     if (rows_lds_bytes(rows.nb, rows.nloc_max, fp64_cg) > static_cast<size_t>(lds_max))
         return fail(c, GSPM_E_ARG, "upload_mesh: the GS row blocks need more LDS than the device has; use smaller "
                                    "block_nodes");
+    // resident solves: the rows' columns for one workgroup per CU
+    c->lds_max = static_cast<size_t>(lds_max);
+    c->cus = 0;
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
+        return fail(c, GSPM_E_DEVICE, "upload_mesh: cannot query the compute units");
+    ResLayoutHost rl;
+    const int32_t res_nbr = resident_rows(hm.n, c->cus);
+    bool resident = res_nbr > 0;
+    if (resident) resident = resident_layout(rows, hm.n, res_nbr, rl);
     // deterministic mode: per owned node its element copies, (copy index within the block's list) << 2 | slot
     std::vector<int32_t> inc_ptr;
     std::vector<uint16_t> inc_ent;
@@ -489,6 +505,15 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
             rc = rc ? rc : dev_alloc(c, &d.det_dst, static_cast<size_t>(kDetSlots));
             rc = rc ? rc : dev_alloc(c, &d.det_count, 1);
         }
+        if (resident) {
+            rc = rc ? rc : dev_alloc(c, &d.res_col, nent);
+            rc = rc ? rc : dev_alloc(c, &d.res_halo_ptr, rl.halo_ptr.size());
+            rc = rc ? rc : dev_alloc(c, &d.res_halo_ids, rl.halo_ids.size());
+            rc = rc ? rc : dev_alloc(c, &d.res_slot, n);
+            rc = rc ? rc : dev_alloc(c, &d.res_xq, resident_xq_bytes(rl.nexp));
+            rc = rc ? rc : dev_alloc(c, &d.res_slots, resident_slot_bytes());
+            rc = rc ? rc : dev_alloc(c, &d.res_epoch, 2);
+        }
         for (int k = 0; k < 2; ++k) {
             rc = rc ? rc : dev_alloc(c, &d.gs_a64[k], nent);
             rc = rc ? rc : dev_alloc(c, &d.gs_d64[k], n);
@@ -556,6 +581,16 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
     hipMemcpyAsync(d.blk_ptr, hm.blk_ptr.data(), sizeof(int32_t) * hm.blk_ptr.size(), hipMemcpyHostToDevice, s);
     hipMemcpyAsync(d.blk_nmag, hm.blk_nmag.data(), sizeof(int32_t) * hm.blk_nmag.size(), hipMemcpyHostToDevice, s);
     hipMemcpyAsync(d.w, hm.w.data(), sizeof(double) * n, hipMemcpyHostToDevice, s);
+    if (resident) {
+        hipMemcpyAsync(d.res_col, rl.col.data(), sizeof(uint16_t) * rl.col.size(), hipMemcpyHostToDevice, s);
+        hipMemcpyAsync(d.res_halo_ptr, rl.halo_ptr.data(), sizeof(int32_t) * rl.halo_ptr.size(), hipMemcpyHostToDevice, s);
+        if (!rl.halo_ids.empty())
+            hipMemcpyAsync(d.res_halo_ids, rl.halo_ids.data(), sizeof(int32_t) * rl.halo_ids.size(), hipMemcpyHostToDevice, s);
+        hipMemcpyAsync(d.res_slot, rl.slot.data(), sizeof(int32_t) * rl.slot.size(), hipMemcpyHostToDevice, s);
+        c->res_gs = ResLayout{d.gs_off, d.res_col, d.res_halo_ptr, d.res_halo_ids, d.res_slot,
+                              hm.n, rl.nbr, rl.G, rl.nhalo_max, rl.nexp};
+        resident_reset(c);
+    }
     hipMemcpyAsync(d.gs_off, rows.off.data(), sizeof(int32_t) * rows.off.size(), hipMemcpyHostToDevice, s);
     hipMemcpyAsync(d.gs_halo_ptr, rows.halo_ptr.data(), sizeof(int32_t) * rows.halo_ptr.size(), hipMemcpyHostToDevice,
                    s);

@@ -6,6 +6,7 @@
 
 #include "common.h"
 #include "mpnn.h"
+#include "resident.h"
 
 namespace gspm {
 
@@ -73,6 +74,12 @@ struct DeviceBuffers {
     double *gs_kv = nullptr, *gs_mv = nullptr, *gs_kd = nullptr, *gs_md = nullptr;
     double *gs_a64[2] = {nullptr, nullptr}, *gs_d64[2] = {nullptr, nullptr};
     float *gs_a32[2] = {nullptr, nullptr}, *gs_d32[2] = {nullptr, nullptr};
+    // resident solves: the GS rows' columns for their workgroups, and the exchange buffers
+    uint16_t *res_col = nullptr;
+    int32_t *res_halo_ptr = nullptr, *res_halo_ids = nullptr;
+    int32_t *res_slot = nullptr;
+    char *res_xq = nullptr, *res_slots = nullptr;
+    uint32_t *res_epoch = nullptr;
 };
 
 // Which (eps, mass) pair a coefficient slot of the GS rows holds.
@@ -162,6 +169,7 @@ struct gspm_ctx {
     struct ProfList {
         std::vector<hipEvent_t> ev;
         std::vector<int> iter;    // CG iteration of each timed pair, -1 = dropped
+        std::vector<int> count;   // iterations the pair covers (1, or a resident solve's)
         size_t used = 0;
     } prof[2];
     int prof_list = -1;
@@ -194,6 +202,13 @@ struct gspm_ctx {
 
     gspm::GreenState pc;                  // elastic preconditioner
 
+    // resident solves (resident_kernel.h): the GS rows' layout (nbr = 0: the mesh is too large for one)
+    gspm::ResLayout res_gs{};
+    gspm::ResResult *h_res = nullptr;     // pinned: the running solve's outcome
+    bool res_off = false;                 // a launch failed or ran out of time: launch-per-iteration from then on
+    size_t lds_max = 0;
+    int cus = 0;
+
     ~gspm_ctx();
     void release_mesh();
     void release_nn();
@@ -213,6 +228,8 @@ CgResult cg_elastic(gspm_ctx *c, double *x, const double *b, double tol, int max
 CgResult cg_gs(gspm_ctx *c, int nc, double eps, double *x, const double *b, double tol, int maxit, SolveKind kind);
 // K^ms x = b (Eq. weak_demag) on nc components, pinned node p0.
 CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int maxit, SolveKind kind);
+// Clears the resident solves' exchange buffers and tags on the context's stream.
+void resident_reset(gspm_ctx *c);
 int run_steps(gspm_ctx *c, double dt, int nsteps, gspm_step_stats *st);
 // The elastic preconditioner: (re)build what the current mesh and parameters
 // need (green.cpp); y = B x on FP64 device vectors [3][n] (FP64 contexts).

@@ -1,0 +1,88 @@
+// CG solves that run to their end in one cooperative launch (resident_kernel.h):
+// the row layout they work on, their exchange buffers and their launcher.
+#pragma once
+
+#include <string>
+#include <vector>
+
+#include "common.h"
+
+namespace gspm {
+
+constexpr int kResThreads = 512;
+constexpr int kResMaxGroups = 256;     // workgroups of a launch, at most one per CU
+constexpr int kFlatGroups = 64;        // up to here every workgroup reads every other's sums
+constexpr int kGroup = 16;             // beyond, groups of this many are summed by a leader first
+constexpr int kMaxSlots = 64;          // sums a workgroup reads at once
+constexpr int kSlotSums = 16;          // sums per slot, 16 bytes each
+constexpr int kResChunks = 3;          // 16-byte chunks per exchanged node: three doubles
+constexpr double kResInnerFloor = 1e-6;
+
+enum ResStatus { RES_OK = 0, RES_NOCONV = 1, RES_NONFINITE = 2, RES_TIMEOUT = 3 };
+
+// Rows of a launch: workgroup g owns rows [g nbr, (g + 1) nbr).  Slices,
+// widths and the entries' order are those of GsRowsHost; col holds the columns
+// as local indices of the workgroup (owned: j - g nbr; halo: nbr + position in
+// its halo list).
+struct ResLayout {
+    const int32_t *off;
+    const uint16_t *col;
+    const int32_t *halo_ptr, *halo_ids;
+    const int32_t *slot;               // n: the node's slot in the exchange buffer, -1 if no other workgroup reads it
+    int32_t n, nbr, G, nhalo_max, nexp;
+};
+
+struct ResLayoutHost {
+    int32_t nbr = 0, G = 0, nhalo_max = 0, nexp = 0;
+    std::vector<uint16_t> col;
+    std::vector<int32_t> halo_ptr, halo_ids;
+    std::vector<int32_t> slot;
+};
+
+// What the host reads back (pinned host memory, written by the launch's end).
+struct ResResult {
+    int32_t status, refinements, stale;
+    int32_t iters[kMaxComp];
+    double relres[kMaxComp];
+};
+
+struct ResArgs {
+    ResLayout ly;
+    const void *a, *d;                 // coefficients and diagonal in the iterations' type
+    const double *a64, *d64;           // and in FP64 (the residuals)
+    double *x;                         // [nc][n] start in, solution out
+    const double *b;
+    const double *bb;                  // |b|^2 per scalar set, sharded
+    double scale;                      // FP32 operator = scale * FP64 operator
+    double tol, tol2;
+    int32_t maxit, jacobi, pinned;
+    void *xq, *slots;
+    uint32_t *epoch;                   // [2]: last tags of the exchange and of the sums
+    ResResult *result;
+    uint32_t stage_bytes;
+};
+
+// The columns of `rows` (any row blocks) for workgroups of nbr rows; false
+// when a workgroup would stage more than 65535 nodes.
+bool resident_layout(const GsRowsHost &rows, int32_t n, int32_t nbr, ResLayoutHost &out);
+// Rows per workgroup (a multiple of 64) for n nodes on a device of `cus` compute units (0: the mesh is too large).
+int32_t resident_rows(int32_t n, int32_t cus);
+// Components of x a residual stages at once.
+__host__ __device__ constexpr int resident_xc(bool f32, int nc, bool blk, int rpt) {
+    return f32 && nc == 3 && !blk && rpt == 8 ? 2 : nc;
+}
+// Sizes of the exchange buffers in bytes.
+__host__ __device__ inline size_t resident_xq_bytes(int32_t nexp) {
+    return 2 * static_cast<size_t>(kResChunks) * 16 * static_cast<size_t>(nexp > 0 ? nexp : 1);
+}
+__host__ __device__ inline size_t resident_slot_bytes() {
+    return 2 * static_cast<size_t>(kResMaxGroups + kGroup) * kSlotSums * 16;
+}
+
+// Whether the launch (type T, nc components, block form) fits the device; fills stage_bytes.
+template <class T>
+bool resident_fits(ResArgs &a, int nc, bool blk, size_t lds_max, int cus);
+template <class T>
+int launch_resident(const ResArgs &a, int nc, bool blk, hipStream_t s);
+
+}  // namespace gspm

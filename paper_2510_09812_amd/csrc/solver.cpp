@@ -138,7 +138,9 @@ const hipEvent_t *prof_begin(gspm_ctx *c, int k) {
         }
     }
     pl.iter.resize(pl.ev.size() / 2);
+    pl.count.resize(pl.ev.size() / 2);
     pl.iter[pl.used / 2] = k;
+    pl.count[pl.used / 2] = 1;
     return &pl.ev[pl.used];
 }
 
@@ -278,6 +280,82 @@ CgResult cg_mixed(gspm_ctx *c, int nc, bool joint, double *x, double tol, int ma
     }
     for (int q = 0; q < ns; ++q) res.iters[q] = total[q];
     return res;
+}
+
+}  // namespace
+
+void resident_reset(gspm_ctx *c) {
+    auto &d = c->d;
+    launch_fill(reinterpret_cast<double *>(d.res_xq), static_cast<int64_t>(resident_xq_bytes(c->res_gs.nexp) / 8), 0.0, c->stream);
+    launch_fill(reinterpret_cast<double *>(d.res_slots), static_cast<int64_t>(resident_slot_bytes() / 8), 0.0, c->stream);
+    launch_fill_i32(reinterpret_cast<int32_t *>(d.res_epoch), 2, 1, c->stream);
+}
+
+namespace {
+
+// A whole solve in one launch (resident_kernel.h): the operator's rows and their
+// layout in `a`, its coefficients in the working type and in FP64.  False when
+// the launch does not fit the device or did not run; nothing has been changed
+// then beyond refinements of x, and the launch-per-iteration path takes over.
+template <class T>
+bool cg_resident(gspm_ctx *c, ResArgs a, int nc, bool blk, double *x, const double *b, double tol, int maxit,
+                 SolveKind kind, CgResult &res) {
+    if (c->res_off || a.ly.nbr == 0) return false;
+    if (!resident_fits<T>(a, nc, blk, c->lds_max, c->cus)) return false;
+    a.x = x;
+    a.b = b;
+    a.bb = c->cg.bb;
+    a.tol = tol;
+    a.tol2 = tol * tol;
+    a.maxit = maxit;
+    a.xq = c->d.res_xq;
+    a.slots = c->d.res_slots;
+    a.epoch = c->d.res_epoch;
+    a.result = c->h_res;
+    hipStream_t s = c->stream;
+    c->h_res->status = RES_TIMEOUT;
+    const hipEvent_t *ev = prof_begin(c, 0);
+    if (ev) hipEventRecord(ev[0], s);
+    const int e = launch_resident<T>(a, nc, blk, s);
+    if (ev) hipEventRecord(ev[1], s);
+    if (e != 0) {
+        (void)hipGetLastError();
+        c->res_off = true;
+        return false;
+    }
+    res = CgResult{};
+    res.status = hip_check(c, hipStreamSynchronize(s), "CG");
+    if (res.status) return true;
+    const ResResult &o = *c->h_res;
+    if (o.stale) resident_reset(c);
+    if (o.status == RES_TIMEOUT) {
+        c->res_off = true;
+        return false;
+    }
+    const int ns = blk ? 1 : nc;
+    int most = 0;
+    double worst = 0.0;
+    for (int q = 0; q < ns; ++q) {
+        res.iters[q] = o.iters[q];
+        most = std::max(most, o.iters[q]);
+        worst = std::max(worst, o.relres[q]);
+    }
+    if (ev) {
+        c->prof[c->prof_list].count[c->prof[c->prof_list].used / 2] = most;
+        prof_end(c);
+    }
+    c->refinements += o.refinements;
+    if (kind == SK_MECH) c->mech_refinements += o.refinements;
+    if (o.status == RES_NOCONV) {
+        res.status = GSPM_E_NOCONV;
+        c->err = "CG did not converge within cg_maxit iterations";
+    } else if (o.status == RES_NONFINITE) {
+        res.status = GSPM_E_NONFINITE;
+        c->err = "non-finite CG residual";
+    } else {
+        c->last_res[kind] = worst;
+    }
+    return true;
 }
 
 }  // namespace
@@ -450,6 +528,24 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
     hipStream_t s = c->stream;
     const bool jac = c->p.gs_precond == GSPM_PRECOND_JACOBI;
     const GsRowsView r64 = gs_rows(c, eps, 1.0, false);
+    const bool mixed = c->precision == GSPM_MIXED;
+    const double ls = c->mv.len_scale, scale = mixed ? 1.0 / (ls * ls * ls) : 1.0;
+    const GsRowsView rw = mixed ? gs_rows(c, eps, 1.0, true) : r64;
+    {
+        ResArgs a{};
+        a.ly = c->res_gs;
+        a.a = rw.a;
+        a.d = rw.d;
+        a.a64 = static_cast<const double *>(r64.a);
+        a.d64 = static_cast<const double *>(r64.d);
+        a.scale = scale;
+        a.jacobi = jac ? 1 : 0;
+        a.pinned = -1;
+        CgResult r;
+        if (mixed ? cg_resident<float>(c, a, nc, false, x, b, tol, maxit, kind, r)
+                  : cg_resident<double>(c, a, nc, false, x, b, tol, maxit, kind, r))
+            return r;
+    }
     auto resid = [&]() {
         launch_gs_rows<double>(c->mv_rows, r64, nc, MV_RESID, x, nullptr, b, c->d.r, c->cg, s);
     };
@@ -466,11 +562,9 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
         };
     };
     auto &d = c->d;
-    if (c->precision == GSPM_MIXED) {
-        const double ls = c->mv.len_scale, scale = 1.0 / (ls * ls * ls);
-        const GsRowsView r32 = gs_rows(c, eps, 1.0, true);
+    if (mixed) {
         return cg_mixed(c, nc, false, x, tol, maxit, kind, scale, resid,
-                        fused(r32, d.r32, d.r32b, d.p32, d.p32b, d.q32, d.q32b, d.x32, c->cg_in, 1.0));
+                        fused(rw, d.r32, d.r32b, d.p32, d.p32b, d.q32, d.q32b, d.x32, c->cg_in, 1.0));
     }
     const size_t first_pair = prof_mark(c);
     CgResult res = cg_fp64(c, nc, false, x, tol, maxit, kind, resid,
@@ -739,7 +833,7 @@ int run_steps(gspm_ctx *c, double dt, int nsteps, gspm_step_stats *st) {
                 float e = 0.0f;
                 hipEventElapsedTime(&e, pl.ev[i], pl.ev[i + 1]);
                 tot += e;
-                ++cnt;
+                cnt += pl.count[i / 2];
             }
             if (li == 0) {
                 st->matvec_ms = tot;
