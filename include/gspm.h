@@ -182,11 +182,12 @@ typedef struct {
     int64_t gs_iters_stage[8]; /* per scalar solve: g1 g2 g3, g*1 g*2, m**1 m**2 m**3 */
     double dm_avg;          /* mean |m^{n+1} - m^n| over magnetic nodes, last step (Sec. 3.2) */
     double elapsed_ms;      /* wall time of the call on the device stream */
-    double matvec_ms;       /* profile mode: summed kernel duration of the working elastic CG
-                               iteration launches (the matvec fused with the CG vector updates, or with
-                               elastic_precond the preconditioned iteration's matvec; those issued after
-                               convergence, which exit at once, excluded) */
-    int64_t matvec_launches;/* profile mode: number of elastic CG iteration launches timed */
+    double matvec_ms;       /* profile mode: summed duration of the elastic CG iterations.  Solves that run in one
+                               launch count that launch whole (residuals and refinements included); otherwise
+                               the kernel durations of the iteration launches (the matvec fused with the CG vector
+                               updates, or with elastic_precond the preconditioned iteration's matvec; those
+                               issued after convergence, which exit at once, excluded) */
+    int64_t matvec_launches;/* profile mode: number of those iterations */
     int64_t refinements;    /* GSPM_MIXED: outer FP64 residual evaluations that started an FP32 inner solve */
     int64_t learned_starts; /* steps whose elastic start used the network's increment */
     int64_t minres_starts; /* steps whose elastic start was a minimum-residual step (learned or extrapolated) */

@@ -217,13 +217,13 @@ gspm_ctx::~gspm_ctx() {
     if (h_flags) hipHostFree(h_flags);
     if (h_mixed) hipHostFree(h_mixed);
     if (h_step) hipHostFree(h_step);
-    if (h_res) hipHostFree(h_res);
     if (own_stream && stream) hipStreamDestroy(stream);
 }
 
 void gspm_ctx::release_mesh() {
     if (stream) hipStreamSynchronize(stream);
     release_pc();
+    release_ops();
     auto &b = d;
     dev_free(this, b.x); dev_free(this, b.lconn); dev_free(this, b.blk_ptr); dev_free(this, b.blk_nmag); dev_free(this, b.w);
     dev_free(this, b.halo_ptr); dev_free(this, b.halo_ids); dev_free(this, b.halo_lo); dev_free(this, b.img);
@@ -248,6 +248,7 @@ void gspm_ctx::release_mesh() {
     dev_free(this, b.res_col); dev_free(this, b.res_halo_ptr); dev_free(this, b.res_halo_ids); dev_free(this, b.res_slot);
     dev_free(this, b.res_xq); dev_free(this, b.res_slots); dev_free(this, b.res_epoch);
     res_gs = gspm::ResLayout{};
+    res_gs_comm = gspm::ResComm{};
     res_off = false;
     dev_free(this, b.gs_off); dev_free(this, b.gs_col); dev_free(this, b.gs_kv); dev_free(this, b.gs_mv);
     dev_free(this, b.gs_kd); dev_free(this, b.gs_md);
@@ -264,6 +265,12 @@ void gspm_ctx::release_mesh() {
     commits = 0;
     tets_int.clear();
     release_nn();
+}
+
+void gspm_ctx::release_ops() {
+    if (stream) hipStreamSynchronize(stream);
+    for (void *p : ops.owned) gspm::ctx_free(this, p);
+    ops = gspm::OperatorRows{};
 }
 
 void gspm_ctx::release_nn() {
@@ -346,10 +353,9 @@ gspm_status gspm_create(gspm_ctx **out, const gspm_create_opts *opts) {
                             hipHostMallocCoherent) == hipSuccess;
     ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_mixed), sizeof(double) * 16 * kShards,
                              hipHostMallocCoherent) == hipSuccess;
-    ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_step), sizeof(double) * 16, hipHostMallocCoherent) ==
-                   hipSuccess;
-    ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_res), sizeof(ResResult), hipHostMallocCoherent) ==
-                   hipSuccess;
+    ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_step), sizeof(double) * 16 + sizeof(ResResult),
+                             hipHostMallocCoherent) == hipSuccess;
+    if (ok) c->h_res = reinterpret_cast<ResResult *>(c->h_step + 16);
     for (auto &e : c->ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreate(&c->t0) == hipSuccess && hipEventCreate(&c->t1) == hipSuccess;
     for (auto &e : c->phase_ev) ok = ok && hipEventCreate(&e) == hipSuccess;
@@ -588,8 +594,9 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
             hipMemcpyAsync(d.res_halo_ids, rl.halo_ids.data(), sizeof(int32_t) * rl.halo_ids.size(), hipMemcpyHostToDevice, s);
         hipMemcpyAsync(d.res_slot, rl.slot.data(), sizeof(int32_t) * rl.slot.size(), hipMemcpyHostToDevice, s);
         c->res_gs = ResLayout{d.gs_off, d.res_col, d.res_halo_ptr, d.res_halo_ids, d.res_slot,
-                              hm.n, rl.nbr, rl.G, rl.nhalo_max, rl.nexp};
-        resident_reset(c);
+                              hm.n, rl.nbr, rl.G, rl.nhalo_max, rl.nexp, rl.wmax};
+        c->res_gs_comm = ResComm{d.res_xq, d.res_slots, d.res_epoch};
+        resident_reset(c, c->res_gs, c->res_gs_comm);
     }
     hipMemcpyAsync(d.gs_off, rows.off.data(), sizeof(int32_t) * rows.off.size(), hipMemcpyHostToDevice, s);
     hipMemcpyAsync(d.gs_halo_ptr, rows.halo_ptr.data(), sizeof(int32_t) * rows.halo_ptr.size(), hipMemcpyHostToDevice,
@@ -725,6 +732,7 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
         c->release_mesh();
         return static_cast<gspm_status>(rc);
     }
+    c->all_magnetic = std::all_of(tags, tags + n_tets, [](uint8_t t) { return t != 0; });
     c->have_mesh = true;
     c->have_m = false;
     return GSPM_OK;
@@ -799,6 +807,9 @@ gspm_status gspm_set_params(gspm_ctx *c, const gspm_params *p) {
         rotate_sym(R, true, ec, c->dargs.csig);
     }
     c->have_params = true;
+    hipSetDevice(c->device);
+    if (p->elastic_precond == GSPM_PRECOND_NONE) operator_rows(c, true);
+    if (p->local_demag) operator_rows(c, false);
     if (p->elastic_precond == GSPM_PRECOND_GREEN) {
         hipSetDevice(c->device);
         const int rc = green_setup(c);

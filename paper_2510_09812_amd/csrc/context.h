@@ -89,6 +89,29 @@ struct GsSlot {
     int64_t used = 0;             // tick of the last use (the least recent slot is rebuilt)
 };
 
+// Exchange buffers of the resident solves on one layout.
+struct ResComm {
+    char *xq = nullptr, *slots = nullptr;
+    uint32_t *epoch = nullptr;
+};
+
+// K^mech and K^ms in row form for the resident solves: the pattern over all
+// elements (built when a solve that uses it is configured or first asked for;
+// the GS rows' own when every element is magnetic), K^mech per stiffness and
+// K^ms once.
+struct OperatorRows {
+    bool tried = false, ready = false;    // the pattern
+    bool k_ready = false, m_ready = false;
+    ResLayout ly{};
+    ResComm comm;
+    int64_t nent = 0;
+    int32_t *inc_ptr = nullptr, *inc = nullptr, *tets = nullptr;
+    double key[36] = {};                  // the stiffness of k64
+    double *k64 = nullptr, *m64 = nullptr;
+    float *k32 = nullptr, *m32 = nullptr;
+    std::vector<void *> owned;            // every device allocation above that is not the GS rows'
+};
+
 // Device state of the learned warm start (allocated on first use).
 struct MpnnState {
     bool ready = false, have_params = false;
@@ -204,7 +227,10 @@ struct gspm_ctx {
 
     // resident solves (resident_kernel.h): the GS rows' layout (nbr = 0: the mesh is too large for one)
     gspm::ResLayout res_gs{};
-    gspm::ResResult *h_res = nullptr;     // pinned: the running solve's outcome
+    gspm::ResComm res_gs_comm;
+    gspm::OperatorRows ops;               // K^mech and K^ms rows
+    bool all_magnetic = false;            // every element is magnetic: the GS rows' pattern is that of all elements
+    gspm::ResResult *h_res = nullptr;     // pinned (after h_step's sums): the running solve's outcome
     bool res_off = false;                 // a launch failed or ran out of time: launch-per-iteration from then on
     size_t lds_max = 0;
     int cus = 0;
@@ -213,6 +239,7 @@ struct gspm_ctx {
     void release_mesh();
     void release_nn();
     void release_pc();
+    void release_ops();
 };
 
 namespace gspm {
@@ -229,7 +256,11 @@ CgResult cg_gs(gspm_ctx *c, int nc, double eps, double *x, const double *b, doub
 // K^ms x = b (Eq. weak_demag) on nc components, pinned node p0.
 CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int maxit, SolveKind kind);
 // Clears the resident solves' exchange buffers and tags on the context's stream.
-void resident_reset(gspm_ctx *c);
+void resident_reset(gspm_ctx *c, const ResLayout &ly, const ResComm &comm);
+// The rows of K^mech (elastic) or K^ms for the resident solves, built when
+// missing or out of date; false when the mesh is too large for them or memory
+// is short (the matrix-free kernels serve then).
+bool operator_rows(gspm_ctx *c, bool elastic);
 int run_steps(gspm_ctx *c, double dt, int nsteps, gspm_step_stats *st);
 // The elastic preconditioner: (re)build what the current mesh and parameters
 // need (green.cpp); y = B x on FP64 device vectors [3][n] (FP64 contexts).

@@ -29,11 +29,11 @@ struct ResLayout {
     const uint16_t *col;
     const int32_t *halo_ptr, *halo_ids;
     const int32_t *slot;               // n: the node's slot in the exchange buffer, -1 if no other workgroup reads it
-    int32_t n, nbr, G, nhalo_max, nexp;
+    int32_t n, nbr, G, nhalo_max, nexp, wmax;   // wmax: entries of the longest row
 };
 
 struct ResLayoutHost {
-    int32_t nbr = 0, G = 0, nhalo_max = 0, nexp = 0;
+    int32_t nbr = 0, G = 0, nhalo_max = 0, nexp = 0, wmax = 0;
     std::vector<uint16_t> col;
     std::vector<int32_t> halo_ptr, halo_ids;
     std::vector<int32_t> slot;
@@ -48,19 +48,45 @@ struct ResResult {
 
 struct ResArgs {
     ResLayout ly;
-    const void *a, *d;                 // coefficients and diagonal in the iterations' type
+    const void *a, *d;                 // coefficients and diagonal (GS) in the iterations' type
     const double *a64, *d64;           // and in FP64 (the residuals)
     double *x;                         // [nc][n] start in, solution out
     const double *b;
     const double *bb;                  // |b|^2 per scalar set, sharded
     double scale;                      // FP32 operator = scale * FP64 operator
     double tol, tol2;
-    int32_t maxit, jacobi, pinned;
+    int32_t maxit, jacobi;
+    int32_t zero_sum;                  // the rows sum to zero (K^mech, K^ms): no diagonals given
     void *xq, *slots;
     uint32_t *epoch;                   // [2]: last tags of the exchange and of the sums
     ResResult *result;
     uint32_t stage_bytes;
+    int32_t lds_entries, lds_threads;  // entries of each lane kept in LDS, and the lanes that have any
 };
+
+// The operators over all elements, K^mech (symmetric 3x3 blocks) and K^ms, in
+// the row form of a layout (operator_rows.hip); null outputs are left out.
+struct OperatorBuild {
+    ResLayout ly;
+    const double *x, *y, *z;
+    double L[3], iL[3];
+    const int32_t *inc_ptr, *inc, *tets;   // elements of each node, ascending; their nodes
+    int32_t p0, parts;
+    double C6[36];                     // stiffness in the sample frame, Voigt
+    double scale_k, scale_m;           // of the FP32 copies
+    double *k64, *m64;
+    float *k32, *m32;
+};
+void launch_operator_rows(OperatorBuild a, hipStream_t s);
+
+// The elements of each node, ascending; false when there are too many to index.
+bool node_elements(int32_t n, const std::vector<int32_t> &tets, std::vector<int32_t> &inc_ptr, std::vector<int32_t> &inc);
+// The pattern of those operators: each node's neighbours through its elements
+// as slices of columns in GsRowsHost's form (blocks of nb rows; no
+// coefficients).  False when a node has 256 or more neighbours or the mesh more
+// entries than the layout addresses.
+bool operator_pattern(int32_t n, const std::vector<int32_t> &tets, const std::vector<int32_t> &inc_ptr,
+                      const std::vector<int32_t> &inc, int32_t nb, GsRowsHost &out);
 
 // The columns of `rows` (any row blocks) for workgroups of nbr rows; false
 // when a workgroup would stage more than 65535 nodes.
@@ -70,6 +96,13 @@ int32_t resident_rows(int32_t n, int32_t cus);
 // Components of x a residual stages at once.
 __host__ __device__ constexpr int resident_xc(bool f32, int nc, bool blk, int rpt) {
     return f32 && nc == 3 && !blk && rpt == 8 ? 2 : nc;
+}
+// Entries of a row each lane keeps in registers: all of a Kuhn mesh's 14 over
+// the whole solve with one row per thread, but four of an FP64 block row (48
+// bytes each); with more rows per thread the size of a buffer that is refilled.
+__host__ __device__ constexpr int resident_entries(bool f32, bool blk, int lanes, int rpt) {
+    const int all = lanes == 1 ? 14 : lanes == 2 ? 7 : 16 / lanes;
+    return !blk ? all : f32 ? (rpt > 1 ? 4 : all) : (lanes >= 4 ? all : 4);
 }
 // Sizes of the exchange buffers in bytes.
 __host__ __device__ inline size_t resident_xq_bytes(int32_t nexp) {

@@ -238,67 +238,73 @@ struct Entries {
     uint16_t c[E];
 };
 
-template <class M, bool BLK, int L, int E>
+// Entries past the row's end take the coefficients of its first (in bounds)
+// and the node `none` for a column (see add_entries).  With END_SELECT that choice is
+// left to add_entries (made here, it would wait for the column's load), with
+// END_BRANCH (whole waves on one slice, one lane per row) they are skipped.
+enum RowEnd { END_LOADED, END_SELECT, END_BRANCH };
+template <class M, bool BLK, int L, int E, RowEnd END>
 __device__ __forceinline__ void load_entries(const M *A, const uint16_t *col, const Slice &sc, int lane, int l, int e0,
-                                             Entries<M, BLK, E> &en) {
+                                             int none, Entries<M, BLK, E> &en) {
+    if (sc.w <= 0) {
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            en.c[u] = static_cast<uint16_t>(none);
+#pragma unroll
+            for (int t = 0; t < (BLK ? 6 : 1); ++t) en.k[u][t] = M(0);
+        }
+        return;
+    }
 #pragma unroll
     for (int u = 0; u < E; ++u) {
         const int e = e0 + u * L + l;
-        const bool in = e < sc.w;
-        const int32_t o = sc.beg + 64 * (in ? e : 0);
-        const int32_t ol = o + lane;
-        en.c[u] = sc.w > 0 ? col[ol] : 0;
+        const int32_t o = sc.beg + 64 * (e < sc.w ? e : 0);
+        const uint16_t c = col[o + lane];
+        en.c[u] = END != END_LOADED || e < sc.w ? c : static_cast<uint16_t>(none);
 #pragma unroll
-        for (int t = 0; t < (BLK ? 6 : 1); ++t) {
-            const M v = sc.w > 0 ? (BLK ? A[static_cast<size_t>(o) * 6 + 64 * t + lane] : A[ol]) : M(0);
-            en.k[u][t] = in ? v : M(0);
-        }
+        for (int t = 0; t < (BLK ? 6 : 1); ++t)
+            en.k[u][t] = BLK ? A[static_cast<size_t>(o) * 6 + 64 * t + lane] : A[o + lane];
     }
 }
 
-template <class M, int NC, bool BLK, int E, class V>
-__device__ __forceinline__ void add_entries(const Entries<M, BLK, E> &en, const V *f, M (&acc)[NC]) {
+// acc += the entries (e0 as they were loaded) times the staged vectors less
+// `base`.  K^mech and K^ms map constants to zero, their diagonals are minus
+// the sum of the row, and base is the row's own vector: rounding of the
+// coefficients then acts on differences between neighbours, as it does in the
+// element form (with a diagonal instead, FP32 rows left ten times the error in
+// the smooth modes).  The GS operator has a diagonal and base is zero.  `none`
+// is a staged node equal to base.
+template <class M, int NC, bool BLK, int L, int E, RowEnd END, class V>
+__device__ __forceinline__ void add_entries(const Entries<M, BLK, E> &en, const Slice &sc, int l, int e0, int none,
+                                            const V *f, const M (&base)[NC], M (&acc)[NC]) {
 #pragma unroll
     for (int u = 0; u < E; ++u) {
-        const V x = f[en.c[u]];
-        if constexpr (BLK) {
-            acc[0] += en.k[u][0] * x.v[0] + en.k[u][5] * x.v[1] + en.k[u][4] * x.v[2];
-            acc[1] += en.k[u][5] * x.v[0] + en.k[u][1] * x.v[1] + en.k[u][3] * x.v[2];
-            acc[2] += en.k[u][4] * x.v[0] + en.k[u][3] * x.v[1] + en.k[u][2] * x.v[2];
-        } else {
+        if (END != END_BRANCH || e0 + u < sc.w) {
+            const V x = f[END != END_SELECT || e0 + u * L + l < sc.w ? en.c[u] : none];
+            M d[NC];
 #pragma unroll
-            for (int q = 0; q < NC; ++q) acc[q] += en.k[u][0] * x.v[q];
+            for (int q = 0; q < NC; ++q) d[q] = x.v[q] - base[q];
+            if constexpr (BLK) {
+                acc[0] += en.k[u][0] * d[0] + en.k[u][5] * d[1] + en.k[u][4] * d[2];
+                acc[1] += en.k[u][5] * d[0] + en.k[u][1] * d[1] + en.k[u][3] * d[2];
+                acc[2] += en.k[u][4] * d[0] + en.k[u][3] * d[1] + en.k[u][2] * d[2];
+            } else {
+#pragma unroll
+                for (int q = 0; q < NC; ++q) acc[q] += en.k[u][0] * d[q];
+            }
         }
     }
-}
-
-// the diagonal's part of a row
-template <class M, int NC, bool BLK, class V>
-__device__ __forceinline__ void add_diagonal(const M (&d)[BLK ? 6 : 1], const V &own, M (&acc)[NC]) {
-    if constexpr (BLK) {
-        acc[0] = d[0] * own.v[0] + d[5] * own.v[1] + d[4] * own.v[2];
-        acc[1] = d[5] * own.v[0] + d[1] * own.v[1] + d[3] * own.v[2];
-        acc[2] = d[4] * own.v[0] + d[3] * own.v[1] + d[2] * own.v[2];
-    } else {
-#pragma unroll
-        for (int q = 0; q < NC; ++q) acc[q] = d[0] * own.v[q];
-    }
-}
-template <class M, bool BLK>
-__device__ __forceinline__ void load_diagonal(const M *D, int n, int g, M (&d)[BLK ? 6 : 1]) {
-#pragma unroll
-    for (int t = 0; t < (BLK ? 6 : 1); ++t) d[t] = D[static_cast<size_t>(t) * n + g];
 }
 
 // the row's entries from e0 on, streamed
 template <class M, int NC, bool BLK, int L, class V>
 __device__ __forceinline__ void add_rest(const M *A, const uint16_t *col, const Slice &sc, int lane, int l, int e0,
-                                         const V *f, M (&acc)[NC]) {
-    constexpr int kE = BLK ? (sizeof(M) == 8 ? 2 : 4) : 8;
+                                         int none, const V *f, const M (&base)[NC], M (&acc)[NC]) {
+    constexpr int kE = BLK ? (sizeof(M) == 8 ? 5 : 4) : 8;
     for (int e = e0; e < sc.w; e += kE * L) {
         Entries<M, BLK, kE> en;
-        load_entries<M, BLK, L, kE>(A, col, sc, lane, l, e, en);
-        add_entries<M, NC, BLK, kE>(en, f, acc);
+        load_entries<M, BLK, L, kE, END_SELECT>(A, col, sc, lane, l, e, none, en);
+        add_entries<M, NC, BLK, L, kE, END_SELECT>(en, sc, l, e, none, f, base, acc);
     }
 }
 
@@ -311,10 +317,10 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     constexpr bool kMixed = sizeof(T) == 4;
     constexpr int NS = BLK ? 1 : NC;
     constexpr int NV = 5 * NS;
-    // entries of a row in registers: all of them over the whole solve with one row per thread (rows of a Kuhn
-    // mesh have 14 off-diagonal entries), else two buffers that take turns
-    constexpr int kAll = L == 1 ? 14 : L == 2 ? 7 : 16 / L;
-    constexpr int E = !BLK ? kAll : sizeof(T) == 4 ? (RPT > 1 ? 4 : kAll) : (L >= 4 ? kAll : 4);
+    constexpr int E = resident_entries(sizeof(T) == 4, BLK, L, RPT);
+    // further entries of FP64 block rows in LDS, as many as fit (see resident_fits); the rest streams
+    constexpr bool kLdsRows = BLK && sizeof(T) == 8 && RPT == 1 && L <= 2;
+    constexpr int kAhead = 5;
     constexpr int kBuf = RPT > 1 ? 2 : 1;
     using V = Vec<T, NC>;
     // components of x staged at once for an FP64 residual: all, but at eight FP32 rows per thread two (LDS)
@@ -330,6 +336,9 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     const int wg = xcd_block(blockIdx.x, G);
     const int n0 = wg * ly.nbr, cnt = min(ly.nbr, n - n0);
     const int hbeg = ly.halo_ptr[wg], nhalo = ly.halo_ptr[wg + 1] - hbeg;
+    const int zero = ly.nbr + nhalo;               // a staged node of zeros
+    // rows that sum to zero: K^mech, K^ms (the only one-component solve)
+    const bool zero_sum = BLK || NC == 1 || (NC == 3 && a.zero_sum != 0);
     const int l = tid & (L - 1), rstep = kTh / L, row00 = tid / L;
     // the row base, hidden from the optimiser in each phase: addresses are formed where they are used instead of
     // being kept in registers (and spilled) for every row over the whole solve
@@ -345,6 +354,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     X *fx = reinterpret_cast<X *>(st);
     T *hr = reinterpret_cast<T *>(st + a.stage_bytes);
     T *hd = hr + static_cast<size_t>(NC) * nhalo;
+    T *sk = hd + ((nhalo + 1) & ~1);               // [entry][6][lane] coefficients, then [entry][lane] columns
+    uint16_t *sc_col = reinterpret_cast<uint16_t *>(sk + 6 * static_cast<size_t>(a.lds_entries) * a.lds_threads);
     const T *A = static_cast<const T *>(a.a), *D = static_cast<const T *>(a.d);
     if (tid == 0) s_bad = s_end = 0;
     uint32_t xt = a.epoch[0], rt = a.epoch[1];
@@ -533,6 +544,22 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         return ng;
     };
 
+    if constexpr (kLdsRows) {
+        // each lane's own entries: no other thread reads them
+        const int row = base_row();
+        if (row < cnt) {
+            const int g = n0 + row;
+            const Slice sc = slice_of(ly, g);
+            for (int u = 0; u < a.lds_entries; ++u) {
+                Entries<T, BLK, 1> one;
+                load_entries<T, BLK, L, 1, END_LOADED>(A, ly.col, sc, g & 63, l, (E + u) * L, row, one);
+#pragma unroll
+                for (int t = 0; t < 6; ++t) sk[(6 * u + t) * a.lds_threads + tid] = one.k[0][t];
+                sc_col[u * a.lds_threads + tid] = one.c[0];
+            }
+        }
+    }
+
     int status = RES_OK, total[NS], refinements = 0;
     double relres[NS];
 #pragma unroll
@@ -588,6 +615,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 for (int c = 0; c < XC; ++c) hv.v[c] = c0 + c < NC ? v[0][c0 + c < NC ? c0 + c : 0] : 0.0;
                 fx[ly.nbr + h] = hv;
             }
+            if (tid == 0) fx[zero] = X{};
             lds_barrier();
             ++xt;
             {
@@ -605,18 +633,21 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 for (int c = 0; c < XC; ++c) bv[c] = c0 + c < NC ? a.b[static_cast<size_t>(c0 + c) * n + g] : 0.0;
 #pragma unroll
                 for (int c = 0; c < XC; ++c) acc[c] = 0.0;
-                if (l == 0) {
-                    double d[BLK ? 6 : 1];
-                    load_diagonal<double, BLK>(a.d64, n, g, d);
-                    add_diagonal<double, XC, BLK>(d, fx[row], acc);
+                double base[XC];
+                const X own = fx[row];
+                const double dg64 = zero_sum ? 0.0 : a.d64[g];
+#pragma unroll
+                for (int c = 0; c < XC; ++c) {
+                    base[c] = zero_sum ? own.v[c] : 0.0;
+                    if (l == 0) acc[c] = dg64 * own.v[c];
                 }
-                add_rest<double, XC, BLK, L>(a.a64, ly.col, slice_of(ly, g), g & 63, l, 0, fx, acc);
+                add_rest<double, XC, BLK, L>(a.a64, ly.col, slice_of(ly, g), g & 63, l, 0, zero_sum ? row : zero, fx, base, acc);
 #pragma unroll
                 for (int c = 0; c < XC; ++c) acc[c] = lanes_sum<L>(acc[c]);
 #pragma unroll
                 for (int c = 0; c < XC; ++c) {
                     if (c0 + c >= NC) continue;
-                    const double rv = BLK && g == a.pinned ? 0.0 : bv[c] - acc[c];
+                    const double rv = bv[c] - acc[c];
                     if (l == 0) part[NS + set(c0 + c)] += rv * rv;
                     r[s][c0 + c] = kMixed ? static_cast<T>(a.scale * rv) : static_cast<T>(rv);
                 }
@@ -705,12 +736,11 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         // --- single-reduction CG
         auto fill = [&](int row, Entries<T, BLK, E> &to) {
             const int g = n0 + (row < cnt ? row : 0);
-            load_entries<T, BLK, L, E>(A, ly.col, slice_of(ly, g), g & 63, l, 0, to);
+            load_entries<T, BLK, L, E, (RPT > 1 ? END_BRANCH : END_LOADED)>(A, ly.col, slice_of(ly, g), g & 63, l, 0, zero_sum ? row : zero, to);
         };
         Entries<T, BLK, E> en[kBuf];
         fill(base_row(), en[0]);
-        T dg[BLK ? 6 : 1];
-        load_diagonal<T, BLK>(D, n, n0 + min(base_row(), cnt - 1), dg);
+        const T dg = zero_sum ? T(0) : D[n0 + min(base_row(), cnt - 1)];
         T al[NC], be[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) al[c] = be[c] = T(0);
@@ -742,6 +772,13 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 }
                 if (!any) break;
                 ended = k == budget;
+            }
+            // the first streamed entries are on their way while the vectors are updated
+            Entries<T, BLK, kLdsRows ? kAhead : 1> ahead;
+            if constexpr (kLdsRows) {
+                const int row = base_row(), g = n0 + (row < cnt ? row : 0);
+                load_entries<T, BLK, L, kAhead, END_SELECT>(A, ly.col, slice_of(ly, g), g & 63, l, (E + a.lds_entries) * L, row, ahead);
+                __builtin_amdgcn_sched_barrier(0);
             }
             // r_k, x_k and p_k = D^-1 r_k + beta p_{k-1} of the rows (x takes alpha p_{k-1})
             {
@@ -809,6 +846,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 }
                 halo(h, q[0]);
             }
+            if (k == 0 && tid == 0) f[zero] = V{};
             lds_barrier();
             // q_k = A p_k and its sums
             ++xt;
@@ -832,18 +870,31 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) acc[c] = T(0);
                 const V p = f[row];
-                T d[BLK ? 6 : 1];
-                if constexpr (RPT > 1) load_diagonal<T, BLK>(D, n, g, d);
-                else for (int t = 0; t < (BLK ? 6 : 1); ++t) d[t] = dg[t];
-                if (l == 0) add_diagonal<T, NC, BLK>(d, p, acc);
-                add_entries<T, NC, BLK, E>(cur, f, acc);
+                const T d = RPT > 1 ? (zero_sum ? T(0) : D[g]) : dg;
+                const int none = zero_sum ? row : zero;
+                T base[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    base[c] = zero_sum ? p.v[c] : T(0);
+                    if (l == 0) acc[c] = d * p.v[c];
+                }
                 const Slice sc = slice_of(ly, g);
-                if (sc.w > E * L) add_rest<T, NC, BLK, L>(A, ly.col, sc, g & 63, l, E * L, f, acc);
+                add_entries<T, NC, BLK, L, E, (RPT > 1 ? END_BRANCH : END_LOADED)>(cur, sc, l, 0, none, f, base, acc);
+                if constexpr (kLdsRows) {
+#pragma unroll 2
+                    for (int u = 0; u < a.lds_entries; ++u) {
+                        Entries<T, BLK, 1> one;
+#pragma unroll
+                        for (int t = 0; t < 6; ++t) one.k[0][t] = sk[(6 * u + t) * a.lds_threads + tid];
+                        one.c[0] = sc_col[u * a.lds_threads + tid];
+                        add_entries<T, NC, BLK, L, 1, END_LOADED>(one, sc, l, 0, none, f, base, acc);
+                    }
+                    add_entries<T, NC, BLK, L, kAhead, END_SELECT>(ahead, sc, l, (E + a.lds_entries) * L, none, f, base, acc);
+                }
+                const int held = (E + (kLdsRows ? a.lds_entries + kAhead : 0)) * L;
+                if (sc.w > held) add_rest<T, NC, BLK, L>(A, ly.col, sc, g & 63, l, held, none, f, base, acc);
 #pragma unroll
                 for (int c = 0; c < NC; ++c) acc[c] = lanes_sum<L>(acc[c]);
-                if (BLK && g == a.pinned)
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) acc[c] = T(0);
                 if (xport[s] >= 0) publish(xport[s], acc);
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
@@ -959,7 +1010,8 @@ const void *entry_of(int nc, bool blk, int nbr) {
 template <class T>
 size_t lds_bytes(const ResArgs &a, int nc, bool blk) {
     const size_t nv = blk ? 5 : 5 * static_cast<size_t>(nc);
-    return sizeof(double) * kMaxSlots * nv + a.stage_bytes + sizeof(T) * (nc + 1) * static_cast<size_t>(a.ly.nhalo_max);
+    return sizeof(double) * kMaxSlots * nv + a.stage_bytes + sizeof(T) * ((nc + 1) * static_cast<size_t>(a.ly.nhalo_max) + 2) +
+           (6 * sizeof(T) + sizeof(uint16_t)) * static_cast<size_t>(a.lds_entries) * a.lds_threads;
 }
 
 }  // namespace
@@ -974,9 +1026,21 @@ bool resident_fits(ResArgs &a, int nc, bool blk, size_t lds_max, int cus) {
     int lanes, rpt;
     shape(ly.nbr, lanes, rpt);
     const size_t per = std::max(sizeof(T) * pad, sizeof(double) * resident_xc(sizeof(T) == 4, nc, blk, rpt));
-    a.stage_bytes = static_cast<uint32_t>((per * (static_cast<size_t>(ly.nbr) + ly.nhalo_max) + 15) / 16 * 16);
+    a.stage_bytes = static_cast<uint32_t>((per * (static_cast<size_t>(ly.nbr) + ly.nhalo_max + 1) + 15) / 16 * 16);
+    a.lds_entries = 0;
+    a.lds_threads = std::min(kTh, (ly.nbr * lanes + 63) / 64 * 64);
     // the kernel's static LDS besides
-    if (lds_bytes<T>(a, nc, blk) + 4096 > lds_max) return false;
+    constexpr size_t kStatic = 4096;
+    if (lds_bytes<T>(a, nc, blk) + kStatic > lds_max) return false;
+    if (blk && sizeof(T) == 8 && rpt == 1 && lanes <= 2) {
+        // At 97k nodes four of 14 FP64 blocks per row are in registers; streaming the other ten (48 MB an iteration,
+        // 6 MB for each XCD's 4 MB of L2) took 14.6 us of a 21 us iteration.  What LDS has left holds five more, and
+        // the last five (24 MB) stay in L2.
+        const int e = resident_entries(false, true, lanes, rpt);
+        const size_t each = (6 * sizeof(T) + sizeof(uint16_t)) * static_cast<size_t>(a.lds_threads);
+        const int most = std::max(0, (ly.wmax + lanes - 1) / lanes - e);
+        a.lds_entries = std::min<int>(most, static_cast<int>((lds_max - kStatic - lds_bytes<T>(a, nc, blk)) / each));
+    }
     int per_cu = 0;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kTh, lds_bytes<T>(a, nc, blk)) == hipSuccess &&
            per_cu >= 1;

@@ -1,11 +1,14 @@
 // CG driver and the GSPM step sequence (host side; all arithmetic runs in
 // the kernels).
 //
-// CG runs without a host round trip per iteration.  The elastic solve, the GS
-// solves and the step's magnetostatic solve run single-reduction CG: one
-// fused launch per iteration, which completes the previous iteration (its
-// scalars summed in the prologue), forms r, p and x in the staging and writes
-// p and q = A p with the next iteration's dot products in the epilogue.
+// CG runs without a host round trip per iteration.  Where the mesh allows it a
+// whole solve is one launch (cg_resident): the GS solves up to 4096 rows per
+// CU, the magnetostatic ones on the same terms, the elastic one up to 1024.
+// Beyond, the elastic solve, the GS solves and the step's magnetostatic solve
+// run single-reduction CG by launches: one fused launch per iteration, which
+// completes the previous iteration (its scalars summed in the prologue), forms
+// r, p and x in the staging and writes p and q = A p with the next iteration's
+// dot products in the epilogue.
 // Multi-component magnetostatic solves (and the preconditioned elastic solve)
 // take separate launches: the matvec, whose staging forms the new direction
 // p_k = z_k + beta_k p_{k-1} after testing ||r_k|| on the device, with p.Ap
@@ -284,11 +287,147 @@ CgResult cg_mixed(gspm_ctx *c, int nc, bool joint, double *x, double tol, int ma
 
 }  // namespace
 
-void resident_reset(gspm_ctx *c) {
-    auto &d = c->d;
-    launch_fill(reinterpret_cast<double *>(d.res_xq), static_cast<int64_t>(resident_xq_bytes(c->res_gs.nexp) / 8), 0.0, c->stream);
-    launch_fill(reinterpret_cast<double *>(d.res_slots), static_cast<int64_t>(resident_slot_bytes() / 8), 0.0, c->stream);
-    launch_fill_i32(reinterpret_cast<int32_t *>(d.res_epoch), 2, 1, c->stream);
+void resident_reset(gspm_ctx *c, const ResLayout &ly, const ResComm &m) {
+    launch_fill(reinterpret_cast<double *>(m.xq), static_cast<int64_t>(resident_xq_bytes(ly.nexp) / 8), 0.0, c->stream);
+    launch_fill(reinterpret_cast<double *>(m.slots), static_cast<int64_t>(resident_slot_bytes() / 8), 0.0, c->stream);
+    launch_fill_i32(reinterpret_cast<int32_t *>(m.epoch), 2, 1, c->stream);
+}
+
+namespace {
+
+// Rows per workgroup up to which K^mech runs in row form: 26 bytes of FP32
+// coefficients and column (50 in FP64) per entry, 14 entries per row, against
+// the strips' 16-bit connectivity.  At 262k nodes that is 95 MB an iteration
+// (184 MB in FP64), which Infinity Cache still holds; at 1M nodes it would be
+// read from HBM in the time the matrix-free kernel takes (82 us).
+constexpr int kResElasticRows = 1024;
+
+// Device memory of the operator rows, several buffers from one allocation:
+// take() in a first pass adds up sizes, in a second hands out the slices.
+struct OpsMemory {
+    char *base = nullptr;
+    size_t used = 0;
+    template <class T>
+    void take(T *&p, size_t count) {
+        if (base) p = reinterpret_cast<T *>(base + used);
+        used += (sizeof(T) * std::max<size_t>(count, 1) + 255) / 256 * 256;
+    }
+};
+
+template <class Layout>
+bool ops_alloc(gspm_ctx *c, Layout layout) {
+    OpsMemory m;
+    layout(m);
+    void *v = nullptr;
+    const std::string err = c->err;
+    if (ctx_malloc(c, &v, m.used, "operator rows")) {
+        (void)hipGetLastError();
+        c->err = err;                     // not a failure of the call: the matrix-free kernels serve
+        return false;
+    }
+    c->ops.owned.push_back(v);
+    m = OpsMemory{static_cast<char *>(v), 0};
+    layout(m);
+    return true;
+}
+
+template <class T>
+bool ops_upload(gspm_ctx *c, T *p, const std::vector<T> &h) {
+    return h.empty() || hipMemcpyAsync(p, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice, c->stream) == hipSuccess;
+}
+
+bool build_pattern(gspm_ctx *c) {
+    auto &o = c->ops;
+    const int32_t nbr = resident_rows(c->n, c->cus);
+    if (nbr == 0 || c->tets_int.empty()) return false;
+    std::vector<int32_t> inc_ptr, inc;
+    if (!node_elements(c->n, c->tets_int, inc_ptr, inc)) return false;
+    // every element magnetic: the GS rows' pattern is this one
+    const bool shared = c->all_magnetic && c->res_gs.nbr == nbr;
+    GsRowsHost rows;
+    ResLayoutHost rl;
+    if (!shared && !(operator_pattern(c->n, c->tets_int, inc_ptr, inc, nbr, rows) &&
+                     resident_layout(rows, c->n, nbr, rl)))
+        return false;
+    int32_t *off = nullptr, *halo_ptr = nullptr, *halo_ids = nullptr, *slot = nullptr;
+    uint16_t *col = nullptr;
+    bool ok = ops_alloc(c, [&](OpsMemory &m) {
+        m.take(o.inc_ptr, inc_ptr.size());
+        m.take(o.inc, inc.size());
+        m.take(o.tets, c->tets_int.size());
+        if (shared) return;
+        m.take(off, rows.off.size());
+        m.take(col, rl.col.size());
+        m.take(halo_ptr, rl.halo_ptr.size());
+        m.take(halo_ids, rl.halo_ids.size());
+        m.take(slot, rl.slot.size());
+        m.take(o.comm.xq, resident_xq_bytes(rl.nexp));
+        m.take(o.comm.slots, resident_slot_bytes());
+        m.take(o.comm.epoch, 2);
+    });
+    ok = ok && ops_upload(c, o.inc_ptr, inc_ptr) && ops_upload(c, o.inc, inc) && ops_upload(c, o.tets, c->tets_int);
+    if (shared) {
+        o.ly = c->res_gs;
+        o.comm = c->res_gs_comm;
+        o.nent = c->gs_nent;
+    } else if (ok) {
+        ok = ops_upload(c, off, rows.off) && ops_upload(c, col, rl.col) && ops_upload(c, halo_ptr, rl.halo_ptr) &&
+             ops_upload(c, halo_ids, rl.halo_ids) && ops_upload(c, slot, rl.slot);
+        o.ly = ResLayout{off, col, halo_ptr, halo_ids, slot, c->n, rl.nbr, rl.G, rl.nhalo_max, rl.nexp, rl.wmax};
+        o.nent = static_cast<int64_t>(rl.col.size());
+        resident_reset(c, o.ly, o.comm);
+    }
+    // the host arrays go out of scope
+    return hipStreamSynchronize(c->stream) == hipSuccess && ok;
+}
+
+}  // namespace
+
+bool operator_rows(gspm_ctx *c, bool elastic) {
+    auto &o = c->ops;
+    if (c->res_off || resident_rows(c->n, c->cus) == 0) return false;
+    if (elastic && resident_rows(c->n, c->cus) > kResElasticRows) return false;
+    if (!o.tried) {
+        o.tried = true;
+        o.ready = build_pattern(c);
+    }
+    if (!o.ready) return false;
+    const bool mixed = c->precision == GSPM_MIXED;
+    if (elastic ? o.k_ready && std::memcmp(o.key, c->mat.C6, sizeof o.key) == 0 : o.m_ready) return true;
+    const size_t ne = static_cast<size_t>(o.nent);
+    OperatorBuild b{};
+    b.ly = o.ly;
+    b.x = c->mv.x; b.y = c->mv.y; b.z = c->mv.z;
+    b.L[0] = c->mv.Lx; b.L[1] = c->mv.Ly; b.L[2] = c->mv.Lz;
+    b.iL[0] = c->mv.iLx; b.iL[1] = c->mv.iLy; b.iL[2] = c->mv.iLz;
+    b.inc_ptr = o.inc_ptr; b.inc = o.inc; b.tets = o.tets;
+    b.p0 = c->p0;
+    std::memcpy(b.C6, c->mat.C6, sizeof b.C6);
+    const double ls = c->mv.len_scale;
+    if (elastic) {
+        if (!o.k64 && !ops_alloc(c, [&](OpsMemory &m) {
+                m.take(o.k64, 6 * ne);
+                if (mixed) m.take(o.k32, 6 * ne);
+            }))
+            return false;
+        b.scale_k = 1.0 / (ls * c->mat.c11);
+        b.k64 = o.k64;
+        b.k32 = o.k32;
+        std::memcpy(o.key, c->mat.C6, sizeof o.key);
+        o.k_ready = true;
+    } else {
+        if (!o.m64 && !ops_alloc(c, [&](OpsMemory &m) {
+                m.take(o.m64, ne);
+                if (mixed) m.take(o.m32, ne);
+            }))
+            return false;
+        b.scale_m = 1.0 / (ls * ls * ls);
+        b.m64 = o.m64;
+        b.m32 = o.m32;
+        o.m_ready = true;
+    }
+    launch_operator_rows(b, c->stream);
+    return true;
 }
 
 namespace {
@@ -298,7 +437,7 @@ namespace {
 // the launch does not fit the device or did not run; nothing has been changed
 // then beyond refinements of x, and the launch-per-iteration path takes over.
 template <class T>
-bool cg_resident(gspm_ctx *c, ResArgs a, int nc, bool blk, double *x, const double *b, double tol, int maxit,
+bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, double *x, const double *b, double tol, int maxit,
                  SolveKind kind, CgResult &res) {
     if (c->res_off || a.ly.nbr == 0) return false;
     if (!resident_fits<T>(a, nc, blk, c->lds_max, c->cus)) return false;
@@ -308,9 +447,9 @@ bool cg_resident(gspm_ctx *c, ResArgs a, int nc, bool blk, double *x, const doub
     a.tol = tol;
     a.tol2 = tol * tol;
     a.maxit = maxit;
-    a.xq = c->d.res_xq;
-    a.slots = c->d.res_slots;
-    a.epoch = c->d.res_epoch;
+    a.xq = comm.xq;
+    a.slots = comm.slots;
+    a.epoch = comm.epoch;
     a.result = c->h_res;
     hipStream_t s = c->stream;
     c->h_res->status = RES_TIMEOUT;
@@ -327,7 +466,7 @@ bool cg_resident(gspm_ctx *c, ResArgs a, int nc, bool blk, double *x, const doub
     res.status = hip_check(c, hipStreamSynchronize(s), "CG");
     if (res.status) return true;
     const ResResult &o = *c->h_res;
-    if (o.stale) resident_reset(c);
+    if (o.stale) resident_reset(c, a.ly, comm);
     if (o.status == RES_TIMEOUT) {
         c->res_off = true;
         return false;
@@ -445,6 +584,22 @@ CgResult cg_elastic(gspm_ctx *c, double *x, const double *b, double tol, int max
         c->prof_list = -1;
         return r;
     }
+    const bool mixed = c->precision == GSPM_MIXED;
+    if (operator_rows(c, true)) {
+        const OperatorRows &o = c->ops;
+        ResArgs a{};
+        a.ly = o.ly;
+        a.a = mixed ? static_cast<const void *>(o.k32) : o.k64;
+        a.a64 = o.k64;
+        a.zero_sum = 1;
+        a.scale = mixed ? 1.0 / (c->mv.len_scale * c->mat.c11) : 1.0;
+        CgResult r;
+        if (mixed ? cg_resident<float>(c, a, o.comm, 3, true, x, b, tol, maxit, kind, r)
+                  : cg_resident<double>(c, a, o.comm, 3, true, x, b, tol, maxit, kind, r)) {
+            c->prof_list = -1;
+            return r;
+        }
+    }
     const size_t first_pair = prof_mark(c);
     hipStream_t s = c->stream;
     auto resid = [&]() {
@@ -463,7 +618,7 @@ CgResult cg_elastic(gspm_ctx *c, double *x, const double *b, double tol, int max
         };
     };
     CgResult r;
-    if (c->precision == GSPM_MIXED) {
+    if (mixed) {
         auto &d = c->d;
         const double scale = 1.0 / (c->mv.len_scale * c->mat.c11);
         r = cg_mixed(c, 3, true, x, tol, maxit, kind, scale, resid,
@@ -540,10 +695,9 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
         a.d64 = static_cast<const double *>(r64.d);
         a.scale = scale;
         a.jacobi = jac ? 1 : 0;
-        a.pinned = -1;
         CgResult r;
-        if (mixed ? cg_resident<float>(c, a, nc, false, x, b, tol, maxit, kind, r)
-                  : cg_resident<double>(c, a, nc, false, x, b, tol, maxit, kind, r))
+        if (mixed ? cg_resident<float>(c, a, c->res_gs_comm, nc, false, x, b, tol, maxit, kind, r)
+                  : cg_resident<double>(c, a, c->res_gs_comm, nc, false, x, b, tol, maxit, kind, r))
             return r;
     }
     auto resid = [&]() {
@@ -580,6 +734,21 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
 // solves' two-launch form with per-component scalars.
 CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int maxit, SolveKind kind) {
     hipStream_t s = c->stream;
+    if (operator_rows(c, false)) {
+        const OperatorRows &o = c->ops;
+        const bool mixed = c->precision == GSPM_MIXED;
+        const double ls = c->mv.len_scale;
+        ResArgs a{};
+        a.ly = o.ly;
+        a.a = mixed ? static_cast<const void *>(o.m32) : o.m64;
+        a.a64 = o.m64;
+        a.zero_sum = 1;
+        a.scale = mixed ? 1.0 / (ls * ls * ls) : 1.0;
+        CgResult r;
+        if (mixed ? cg_resident<float>(c, a, o.comm, nc, false, x, b, tol, maxit, kind, r)
+                  : cg_resident<double>(c, a, o.comm, nc, false, x, b, tol, maxit, kind, r))
+            return r;
+    }
     auto resid = [&]() {
         launch_ms_matvec<double>(c->mv, nc, MV_RESID, x, nullptr, b, c->d.r, nullptr, c->cg, 0, tol, s);
     };
