@@ -246,7 +246,8 @@ struct GreenView {
     const int32_t *rgrid;         // the grid point of row t (rows run in Morton order of the grid points)
     const void *rw;               // their weights (T)
     const void *dinv;             // [3][n] omega / diag(K^mech) (T)
-    const void *ainv;             // [Gh][9] A(k)^-1 / G, Hermitian: re a00 a11 a22, then a01 a02 a12 (re, im) (T)
+    const void *ainv;             // A(k)^-1 / G, Hermitian: re a00 a11 a22, then a01 a02 a12 (re, im) (T); [Gh][9], or as
+                                  // the own transforms read it (launch_pc_symbol)
     void *grid;                   // [2][G] complex (T): x0 + i x1, x2 on the grid (restriction in, prolongation out)
     void *spec;                   // [2][G] complex (T): their spectra (forward FFT out, inverse FFT in)
 };
@@ -270,9 +271,11 @@ void launch_remove_mean3(int n, double *b, double *aux, double *bb, hipStream_t 
 void launch_pin_shift(int n, double *x, int p0, double *aux, hipStream_t s);
 // The symbol inverse of the grid operator for the half spectrum: stencil27 is
 // the 27 3x3 blocks S(o) (o = (ox, oy, oz) in {-1,0,1}^3, index (oz+1)*9 + (oy+1)*3 + (ox+1)),
-// A(k) = sum_o S(o) exp(2 pi i k.o / g), stored as A(k)^-1 * factor (zero at k = 0).
+// A(k) = sum_o S(o) exp(2 pi i k.o / g), stored as A(k)^-1 * factor (zero at k
+// = 0): by mode, or with fp (the own transforms) as [9][position along z][pair].
+struct FftPlan;
 template <class T>
-void launch_pc_symbol(const GreenView &gv, const double *stencil27, double factor, hipStream_t s);
+void launch_pc_symbol(const GreenView &gv, const FftPlan *fp, const double *stencil27, double factor, hipStream_t s);
 // Preconditioned CG iteration k on the elastic system: p_k = z_k + beta p_{k-1}
 // (beta = rz[k] / rz[k-1], p_0 = z_0) in the staging, q = A p_k (no pinned
 // node), pq[k] += p_k . q.  pin = p_{k-1}, pout = p_k (alternating buffers).

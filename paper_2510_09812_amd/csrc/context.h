@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "common.h"
+#include "green_fft.h"
 #include "mpnn.h"
 #include "resident.h"
 
@@ -141,6 +142,9 @@ struct GreenState {
     void *rw = nullptr, *dinv = nullptr, *ainv = nullptr, *grid = nullptr, *spec = nullptr, *work = nullptr;
     double *aux = nullptr;        // 3 x kShards: mean sums; then 3: the pinned node's shift
     size_t work_bytes = 0;
+    bool own_fft = false;         // the transforms of green_fft.hip (fft, tables); else rocFFT's
+    FftPlan fft{};
+    void *tables = nullptr;
     void *fwd = nullptr, *inv = nullptr, *info = nullptr;   // rocfft_plan, rocfft_plan, rocfft_execution_info
 };
 
@@ -270,9 +274,11 @@ int green_setup(gspm_ctx *c);
 // the pair is not cached.
 GsRowsView gs_rows(gspm_ctx *c, double eps, double mass, bool fp32);
 int green_apply64(gspm_ctx *c, const double *x, double *y);
-// FFTs of the preconditioner on the context's stream, the two packed complex
-// grids as one batch: grid -> spec (forward) or spec -> grid (inverse).
-int green_fft(gspm_ctx *c, bool forward);
+// z = B r on the context's stream, T the preconditioner's precision: tests |r|
+// as iteration test_k first (test_k < 0: no test) and does nothing once
+// converged; rz += r.z.
+template <class T>
+int green_precond(gspm_ctx *c, const T *r, T *z, double *rz, const CGScalars &cg, int test_k, double tol);
 int hip_check(gspm_ctx *c, hipError_t e, const char *what);
 // Device memory of the context: the caller's allocator when given, else hipMalloc / hipFree.
 int ctx_malloc(gspm_ctx *c, void **p, size_t bytes, const char *what);

@@ -5,8 +5,8 @@
 // elastic system by unpreconditioned CG and names that solve as the cost to
 // cut (Sec. 5.2); the stiffness is one homogeneous C on a periodic cell, so
 // the Green's operator of C on a regular periodic grid is close to its
-// inverse.  The FFTs are plain library transforms (rocFFT); every other pass
-// is a kernel of green_kernels.hip.
+// inverse.  The transforms and modes are the kernels of green_fft.hip where
+// their planes fit LDS, else library transforms (rocFFT) around k_pc_modes.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -140,6 +140,98 @@ int make_plans(gspm_ctx *c, bool f32) {
     return GSPM_OK;
 }
 
+// n = n1 n2 with the factors nearest to each other, n1 <= n2.
+void split(int n, int &n1, int &n2) {
+    n1 = 1;
+    for (int f = 2; f * f <= n; ++f)
+        if (n % f == 0) n1 = f;
+    n2 = n / n1;
+}
+
+// The weights, twiddles and position tables of the three axes and the
+// column pairs, in one allocation.
+template <class T>
+int make_tables(gspm_ctx *c) {
+    auto &pc = c->pc;
+    const int g[3] = {pc.gv.gx, pc.gv.gy, pc.gv.gz};
+    FftAxis *ax[3] = {&pc.fft.x, &pc.fft.y, &pc.fft.z};
+    std::vector<T> cx;
+    std::vector<int32_t> ix;
+    size_t at[3][3], iat[3][2];
+    auto root = [&](int64_t k, int n, double sign) {
+        const double ph = 6.283185307179586476925286766559 * static_cast<double>(k % n) / n;
+        cx.push_back(static_cast<T>(std::cos(ph)));
+        cx.push_back(static_cast<T>(sign * std::sin(ph)));
+    };
+    auto weights = [&](int R) {
+        for (int t = 0; t <= R / 2; ++t)
+            for (int k = 0; k < fft_columns(R); ++k) root(static_cast<int64_t>(k) * t, R, 1.0);
+    };
+    std::vector<int32_t> neg[3], freq[3], pos[3];
+    for (int a = 0; a < 3; ++a) {
+        int n1, n2;
+        split(g[a], n1, n2);
+        ax[a]->n1 = n1;
+        ax[a]->n2 = n2;
+        at[a][0] = cx.size();
+        weights(n1);
+        at[a][1] = cx.size();
+        weights(n2);
+        at[a][2] = cx.size();
+        for (int t = 0; t < n2; ++t)
+            for (int k = 0; k < n1; ++k) root(static_cast<int64_t>(t) * k, g[a], -1.0);
+        freq[a].resize(g[a]);
+        pos[a].resize(g[a]);
+        neg[a].resize(g[a]);
+        for (int k1 = 0; k1 < n1; ++k1)
+            for (int k2 = 0; k2 < n2; ++k2) {
+                freq[a][k1 * n2 + k2] = k1 + n1 * k2;
+                pos[a][k1 + n1 * k2] = k1 * n2 + k2;
+            }
+        for (int q = 0; q < g[a]; ++q) neg[a][q] = pos[a][(g[a] - freq[a][q]) % g[a]];
+        iat[a][0] = ix.size();
+        ix.insert(ix.end(), freq[a].begin(), freq[a].end());
+        iat[a][1] = ix.size();
+        ix.insert(ix.end(), neg[a].begin(), neg[a].end());
+    }
+    // column pairs (ky, kx), kx in the half spectrum, each with its mirror once; in the order of the column's
+    // position, so that a workgroup's columns are mostly consecutive
+    while (ix.size() % 4) ix.push_back(0);
+    const size_t pat = ix.size();
+    pc.fft.npairs = 0;
+    for (int qy = 0; qy < g[1]; ++qy)
+        for (int qx = 0; qx < g[0]; ++qx) {
+            const int kx = freq[0][qx], ky = freq[1][qy], mx = (g[0] - kx) % g[0], my = (g[1] - ky) % g[1];
+            if (kx >= pc.gv.gxh) continue;
+            if (mx < pc.gv.gxh && static_cast<int64_t>(my) * g[0] + mx < static_cast<int64_t>(ky) * g[0] + kx) continue;
+            ix.push_back(qy * g[0] + qx);
+            ix.push_back(neg[1][qy] * g[0] + neg[0][qx]);
+            ix.push_back(kx);
+            ix.push_back(ky);
+            ++pc.fft.npairs;
+        }
+    const size_t cb = (sizeof(T) * cx.size() + 255) / 256 * 256;
+    char *base = nullptr;
+    int rc = pc_alloc(c, &base, cb + sizeof(int32_t) * ix.size());
+    if (rc) return rc;
+    pc.tables = base;
+    hipMemcpyAsync(base, cx.data(), sizeof(T) * cx.size(), hipMemcpyHostToDevice, c->stream);
+    hipMemcpyAsync(base + cb, ix.data(), sizeof(int32_t) * ix.size(), hipMemcpyHostToDevice, c->stream);
+    rc = hip_check(c, hipStreamSynchronize(c->stream), "elastic preconditioner setup");
+    if (rc) return rc;
+    const T *cd = reinterpret_cast<const T *>(base);
+    const int32_t *id = reinterpret_cast<const int32_t *>(base + cb);
+    for (int a = 0; a < 3; ++a) {
+        ax[a]->cs1 = cd + at[a][0];
+        ax[a]->cs2 = cd + at[a][1];
+        ax[a]->tw = cd + at[a][2];
+        ax[a]->freq = id + iat[a][0];
+        ax[a]->neg = id + iat[a][1];
+    }
+    pc.fft.pairs = id + pat;
+    return GSPM_OK;
+}
+
 // The grid and the restriction lists: grid point g gathers every node whose
 // trilinear corners include g, with that corner's weight.
 int setup_mesh_part(gspm_ctx *c) {
@@ -191,6 +283,13 @@ int setup_mesh_part(gspm_ctx *c) {
                                                    ((cc & 4) ? t[2] : 1.0 - t[2]);
         }
     }
+    // the transforms: the library's only where planes or columns do not fit LDS (above about 140 points per axis in
+    // FP32, 100 in FP64).  Where they fit the own ones are the faster: an application's transforms and modes take
+    // 34 us against 165 at 46^3 (FP32) and 79 against 87 at 99^3
+    int n1[3], n2[3];
+    for (int a = 0; a < 3; ++a) split(g[a], n1[a], n2[a]);
+    pc.fft.wg_pairs = green_fft_fits(gv, n1, n2, f32, c->lds_max);
+    pc.own_fft = pc.fft.wg_pairs > 0;
     // rows of the restriction run over the grid points in Morton order (the
     // nodes are Morton-numbered, so consecutive rows gather nearby nodes)
     auto spread = [](uint64_t v) {
@@ -256,7 +355,7 @@ int setup_mesh_part(gspm_ctx *c) {
     gv.ainv = pc.ainv;
     gv.grid = pc.grid;
     gv.spec = pc.spec;
-    rc = make_plans(c, f32);
+    rc = pc.own_fft ? (f32 ? make_tables<float>(c) : make_tables<double>(c)) : make_plans(c, f32);
     if (rc) return rc;
     pc.mesh_ready = true;
     return GSPM_OK;
@@ -324,9 +423,9 @@ int green_setup(gspm_ctx *c) {
     double S[27 * 9];
     grid_stencil(c->mat.C6, pc.gv.h, S);
     if (f32)
-        launch_pc_symbol<float>(pc.gv, S, factor / static_cast<double>(pc.gv.G), c->stream);
+        launch_pc_symbol<float>(pc.gv, pc.own_fft ? &pc.fft : nullptr, S, factor / static_cast<double>(pc.gv.G), c->stream);
     else
-        launch_pc_symbol<double>(pc.gv, S, factor / static_cast<double>(pc.gv.G), c->stream);
+        launch_pc_symbol<double>(pc.gv, pc.own_fft ? &pc.fft : nullptr, S, factor / static_cast<double>(pc.gv.G), c->stream);
     int rc = setup_diagonal(c, factor, f32);
     if (rc) return rc;
     std::memcpy(pc.sym_key, key, sizeof key);
@@ -334,7 +433,9 @@ int green_setup(gspm_ctx *c) {
     return GSPM_OK;
 }
 
-int green_fft(gspm_ctx *c, bool forward) {
+namespace {
+
+int library_fft(gspm_ctx *c, bool forward) {
     auto &pc = c->pc;
     void *in[1] = {forward ? pc.grid : pc.spec};
     void *out[1] = {forward ? pc.spec : pc.grid};
@@ -343,18 +444,32 @@ int green_fft(gspm_ctx *c, bool forward) {
     return st == rocfft_status_success ? GSPM_OK : fft_fail(c, "rocfft_execute failed");
 }
 
-int green_apply64(gspm_ctx *c, const double *x, double *y) {
+}  // namespace
+
+template <class T>
+int green_precond(gspm_ctx *c, const T *r, T *z, double *rz, const CGScalars &cg, int test_k, double tol) {
     auto &pc = c->pc;
+    int rc = GSPM_OK;
+    launch_pc_restrict<T>(pc.gv, c->n, r, cg, test_k, tol, c->stream);
+    if (pc.own_fft) {
+        launch_pc_fft<T>(pc.gv, pc.fft, cg, c->stream);
+    } else {
+        rc = library_fft(c, true);
+        launch_pc_modes<T>(pc.gv, cg, c->stream);
+        rc = rc ? rc : library_fft(c, false);
+    }
+    launch_pc_prolong<T>(pc.gv, c->mv, r, z, rz, cg, c->stream);
+    return rc;
+}
+
+template int green_precond<double>(gspm_ctx *, const double *, double *, double *, const CGScalars &, int, double);
+template int green_precond<float>(gspm_ctx *, const float *, float *, double *, const CGScalars &, int, double);
+
+int green_apply64(gspm_ctx *c, const double *x, double *y) {
     // a fresh scalar set: the passes test nothing (test_k < 0) and run
     cg_prepare(c, 1);
-    launch_pc_restrict<double>(pc.gv, c->n, x, c->cg, -1, 0.0, c->stream);
-    int rc = green_fft(c, true);
-    if (rc) return rc;
-    launch_pc_modes<double>(pc.gv, c->cg, c->stream);
-    rc = green_fft(c, false);
-    if (rc) return rc;
-    launch_pc_prolong<double>(pc.gv, c->mv, x, y, c->cg.rq_at(0), c->cg, c->stream);
-    return hip_check(c, hipStreamSynchronize(c->stream), "apply(PRECOND)");
+    const int rc = green_precond<double>(c, x, y, c->cg.rq_at(0), c->cg, -1, 0.0);
+    return rc ? rc : hip_check(c, hipStreamSynchronize(c->stream), "apply(PRECOND)");
 }
 
 }  // namespace gspm
@@ -366,7 +481,7 @@ void gspm_ctx::release_pc() {
     if (q.inv) rocfft_plan_destroy(static_cast<rocfft_plan>(q.inv));
     if (q.info) rocfft_execution_info_destroy(static_cast<rocfft_execution_info>(q.info));
     for (void *p : {static_cast<void *>(q.rptr), static_cast<void *>(q.rgrid), static_cast<void *>(q.rnode), q.rw,
-                    q.dinv, q.ainv, q.grid, q.spec, q.work, static_cast<void *>(q.aux)})
+                    q.dinv, q.ainv, q.grid, q.spec, q.work, q.tables, static_cast<void *>(q.aux)})
         gspm::ctx_free(this, p);
     q = gspm::GreenState{};
 }

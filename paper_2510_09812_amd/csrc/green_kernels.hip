@@ -6,6 +6,7 @@
 // component-major [3][n], grid arrays [3][G] real and [3][Gh] complex, so the
 // FFTs run as one batch of three.
 #include "device_common.h"
+#include "green_fft.h"
 
 namespace gspm {
 
@@ -268,17 +269,21 @@ struct Stencil27 {
 };
 
 template <class T>
-__global__ void __launch_bounds__(kThreads) k_pc_symbol(GreenView gv, Stencil27 st, double factor) {
+__global__ void __launch_bounds__(kThreads) k_pc_symbol(GreenView gv, FftPlan fp, Stencil27 st, double factor) {
     T *out = static_cast<T *>(const_cast<void *>(gv.ainv));
-    for (int64_t m = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; m < gv.Gh;
+    // by mode of the half spectrum, or (fp.pairs) by position along z and column pair
+    const int64_t count = fp.pairs ? static_cast<int64_t>(fp.npairs) * gv.gz : gv.Gh;
+    for (int64_t m = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; m < count;
          m += static_cast<int64_t>(gridDim.x) * kThreads) {
-        const int kx = static_cast<int>(m % gv.gxh);
-        const int ky = static_cast<int>((m / gv.gxh) % gv.gy);
-        const int kz = static_cast<int>(m / (static_cast<int64_t>(gv.gxh) * gv.gy));
-        T *o = out + 9 * m;
-        if (m == 0) {
+        const int pair = fp.pairs ? static_cast<int>(m % fp.npairs) : 0;
+        const int kx = fp.pairs ? fp.pairs[4 * pair + 2] : static_cast<int>(m % gv.gxh);
+        const int ky = fp.pairs ? fp.pairs[4 * pair + 3] : static_cast<int>((m / gv.gxh) % gv.gy);
+        const int kz = fp.pairs ? fp.z.freq[m / fp.npairs] : static_cast<int>(m / (static_cast<int64_t>(gv.gxh) * gv.gy));
+        T *o = fp.pairs ? out + m : out + 9 * m;
+        const int64_t os = fp.pairs ? count : 1;
+        if (kx == 0 && ky == 0 && kz == 0) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) o[q] = T(0);
+            for (int q = 0; q < 9; ++q) o[q * os] = T(0);
             continue;
         }
         double ar[3][3] = {}, ai[3][3] = {};
@@ -324,15 +329,15 @@ __global__ void __launch_bounds__(kThreads) k_pc_symbol(GreenView gv, Stencil27 
         // inverse(i, j) = C(j, i) / det
         auto inv_re = [&](int i, int j) { return (cr[j][i] * dr + ci[j][i] * di) / den * factor; };
         auto inv_im = [&](int i, int j) { return (ci[j][i] * dr - cr[j][i] * di) / den * factor; };
-        o[0] = static_cast<T>(inv_re(0, 0));
-        o[1] = static_cast<T>(inv_re(1, 1));
-        o[2] = static_cast<T>(inv_re(2, 2));
-        o[3] = static_cast<T>(inv_re(0, 1));
-        o[4] = static_cast<T>(inv_im(0, 1));
-        o[5] = static_cast<T>(inv_re(0, 2));
-        o[6] = static_cast<T>(inv_im(0, 2));
-        o[7] = static_cast<T>(inv_re(1, 2));
-        o[8] = static_cast<T>(inv_im(1, 2));
+        o[0 * os] = static_cast<T>(inv_re(0, 0));
+        o[1 * os] = static_cast<T>(inv_re(1, 1));
+        o[2 * os] = static_cast<T>(inv_re(2, 2));
+        o[3 * os] = static_cast<T>(inv_re(0, 1));
+        o[4 * os] = static_cast<T>(inv_im(0, 1));
+        o[5 * os] = static_cast<T>(inv_re(0, 2));
+        o[6 * os] = static_cast<T>(inv_im(0, 2));
+        o[7 * os] = static_cast<T>(inv_re(1, 2));
+        o[8 * os] = static_cast<T>(inv_im(1, 2));
     }
 }
 
@@ -376,10 +381,10 @@ void launch_pin_shift(int n, double *x, int p0, double *aux, hipStream_t s) {
 }
 
 template <class T>
-void launch_pc_symbol(const GreenView &gv, const double *stencil27, double factor, hipStream_t s) {
+void launch_pc_symbol(const GreenView &gv, const FftPlan *fp, const double *stencil27, double factor, hipStream_t s) {
     Stencil27 st;
     for (int q = 0; q < 27 * 9; ++q) st.s[q] = stencil27[q];
-    hipLaunchKernelGGL(k_pc_symbol<T>, dim3(grid_of(gv.Gh)), dim3(kThreads), 0, s, gv, st, factor);
+    hipLaunchKernelGGL(k_pc_symbol<T>, dim3(grid_of(gv.Gh)), dim3(kThreads), 0, s, gv, fp ? *fp : FftPlan{}, st, factor);
 }
 
 #define GSPM_PC_INST(T)                                                                                              \
@@ -389,7 +394,7 @@ void launch_pc_symbol(const GreenView &gv, const double *stencil27, double facto
     template void launch_pc_prolong<T>(const GreenView &, const MeshView &, const T *, T *, double *,               \
                                        const CGScalars &, hipStream_t);                                             \
     template void launch_pcg_update<T>(int, T *, T *, const T *, const T *, const CGScalars &, int, hipStream_t);  \
-    template void launch_pc_symbol<T>(const GreenView &, const double *, double, hipStream_t);
+    template void launch_pc_symbol<T>(const GreenView &, const FftPlan *, const double *, double, hipStream_t);
 GSPM_PC_INST(double)
 GSPM_PC_INST(float)
 #undef GSPM_PC_INST

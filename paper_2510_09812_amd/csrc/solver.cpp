@@ -517,13 +517,8 @@ auto pcg_iteration(gspm_ctx *c, const MeshView &mvu, T *x, T *r, T *z, T *pa, T 
     return [=](int k, bool last) {
         if (last) return;                  // |r| of the last iteration was tested by its own preconditioner pass
         hipStream_t s = c->stream;
-        const GreenView &gv = c->pc.gv;
         auto precond = [&](int test_k) {
-            launch_pc_restrict<T>(gv, c->n, r, cg, test_k, tol, s);
-            int rc = green_fft(c, true);
-            launch_pc_modes<T>(gv, cg, s);
-            rc = rc ? rc : green_fft(c, false);
-            launch_pc_prolong<T>(gv, c->mv, r, z, pcg_rz_at(cg, test_k), cg, s);
+            const int rc = green_precond<T>(c, r, z, pcg_rz_at(cg, test_k), cg, test_k, tol);
             if (rc && !*fft_rc) *fft_rc = rc;
         };
         if (k == 0 || c->pc_owed) {
