@@ -117,6 +117,7 @@ struct OperatorRows {
 struct MpnnState {
     bool ready = false, have_params = false;
     int32_t *gptr = nullptr, *gnbr = nullptr;
+    float *gedge = nullptr;
     int64_t nedges = 0;
     float *master = nullptr, *wr = nullptr, *m1 = nullptr, *m2 = nullptr, *grad = nullptr;
     uint16_t *mats = nullptr, *acts = nullptr;

@@ -69,6 +69,7 @@ int nn_setup(gspm_ctx *c) {
     const size_t n = static_cast<size_t>(c->n);
     int rc = 0;
     rc = rc ? rc : nn_alloc(c, &nn.gptr, ptr.size());
+    rc = rc ? rc : nn_alloc(c, &nn.gedge, 4 * nbr.size());
     rc = rc ? rc : nn_alloc(c, &nn.gnbr, nbr.size());
     rc = rc ? rc : nn_alloc(c, &nn.master, kNParam);
     rc = rc ? rc : nn_alloc(c, &nn.wr, kNParam);
@@ -87,7 +88,7 @@ int nn_setup(gspm_ctx *c) {
     rc = rc ? rc : nn_alloc(c, &nn.gha, n * 128);
     rc = rc ? rc : nn_alloc(c, &nn.gab, n * 128);
     rc = rc ? rc : nn_alloc(c, &nn.gy, 3 * n);
-    nn.part_wgs = static_cast<int>(std::min<size_t>(512, std::max<size_t>(1, (n + 255) / 256)));
+    nn.part_wgs = static_cast<int>(std::min<size_t>(256, std::max<size_t>(1, (n + 127) / 128)));
     rc = rc ? rc : nn_alloc(c, &nn.part, static_cast<size_t>(nn.part_wgs) * kPartStride);
     if (rc) {
         c->release_nn();
@@ -96,15 +97,16 @@ int nn_setup(gspm_ctx *c) {
     hipStream_t s = c->stream;
     hipMemcpyAsync(nn.gptr, ptr.data(), sizeof(int32_t) * ptr.size(), hipMemcpyHostToDevice, s);
     hipMemcpyAsync(nn.gnbr, nbr.data(), sizeof(int32_t) * std::max<size_t>(nbr.size(), 1), hipMemcpyHostToDevice, s);
+    nn.nedges = static_cast<int64_t>(nbr.size());
+    // mean spacing: the edge of a cube split into 6 tetrahedra of the mean volume
+    const double hbar = std::cbrt(6.0 * c->vc / static_cast<double>(c->ne));
+    nn.graph = Graph{nn.gptr, nn.gedge, c->n, static_cast<float>(1.0 / hbar)};
+    mpnn::launch_edges(nn.graph, c->mv, nn.gnbr, nn.gedge, s);
     rc = hip_check(c, hipStreamSynchronize(s), "network setup");
     if (rc) {
         c->release_nn();
         return rc;
     }
-    nn.nedges = static_cast<int64_t>(nbr.size());
-    // mean spacing: the edge of a cube split into 6 tetrahedra of the mean volume
-    const double hbar = std::cbrt(6.0 * c->vc / static_cast<double>(c->ne));
-    nn.graph = Graph{nn.gptr, nn.gnbr, c->n, static_cast<float>(1.0 / hbar)};
     nn.net = Net{nn.wr, nn.mats};
     uint16_t *a = nn.acts;
     for (int l = 0; l <= kLayers; ++l, a += n * kHid) nn.A.H[l] = a;

@@ -23,7 +23,7 @@ constexpr int kLWa = 0, kLWb = kHid * kHid, kLWe = 2 * kHid * kHid, kLC = kLWe +
 constexpr int kOffWd = kOffL0 + kLayers * kLayerSize, kOffBd = kOffWd + kOut * kHid, kNParam = kOffBd + kOut;
 static_assert(kNParam == 50819, "parameter layout");
 constexpr int kMat = 128 * 64;              // elements of each BF16 weight-matrix form
-constexpr int kPartStride = 8192;           // floats of one workgroup's gradient partial
+constexpr int kPartStride = (kNParam + 63) / 64 * 64;   // floats of one workgroup's gradient partial, laid out as the parameters
 
 // Reduction slots (each kShards doubles) of the network's scalar buffer.
 enum RedSlot { R_DM2 = 0, R_W = 1, R_Y = 2, R_T = 5, R_LOSS = 8, R_COUNT = 9 };
@@ -31,7 +31,8 @@ enum RedSlot { R_DM2 = 0, R_W = 1, R_Y = 2, R_T = 5, R_LOSS = 8, R_COUNT = 9 };
 enum MrSlot { G_DKD = 0, G_DKE = 1, G_EKE = 2, G_DR = 3, G_ER = 4, kMrSums = 5 };   // Kd.Kd, Kd.Ke, Ke.Ke, Kd.r0, Ke.r0
 
 struct Graph {
-    const int32_t *ptr, *nbr;                // CSR over unique nodes, neighbours sorted
+    const int32_t *ptr;                      // CSR over unique nodes, neighbours sorted
+    const float *edge;                       // per directed edge: (x_j - x_i) / hbar, bits of j
     int32_t n;
     float ihbar;                             // 1 / mean spacing: edge vectors are (x_j - x_i) / hbar
 };
@@ -52,7 +53,7 @@ struct Acts {
 
 struct Grads {
     float *gh;                               // n x 64
-    float *gha;                              // n x 128: d[h ; a]
+    float *gha;                              // n x 128: d[h | a / degree]
     float *gab;                              // n x 128: d[A | B]
     float *gy;                               // n x 3
     float *part;                             // per-workgroup partials, kPartStride each
@@ -81,6 +82,9 @@ void launch_minres(int n, const double *d, const double *kd, const double *e, co
                      double *x, double *red, double *coef, hipStream_t s);
 // out = a - b over n3 values.
 void launch_sub(int64_t n3, const double *a, const double *b, double *out, hipStream_t s);
+
+// The edges' vectors and neighbours, from the neighbour lists.
+void launch_edges(const Graph &g, const MeshView &mv, const int32_t *nbr, float *edge, hipStream_t s);
 
 // Host: directed edge graph of the mesh on unique nodes (every pair of
 // distinct nodes sharing a tetrahedron, both directions), CSR with sorted
