@@ -95,20 +95,6 @@ bool all_finite(const double *v, size_t n) {
     return true;
 }
 
-int upload(gspm_ctx *c, double *dst, const std::vector<double> &h) {
-    int rc = hip_check(c, hipMemcpyAsync(dst, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, c->stream),
-                       "copy to device");
-    if (rc) return rc;
-    return hip_check(c, hipStreamSynchronize(c->stream), "copy to device");
-}
-
-int download(gspm_ctx *c, const double *src, std::vector<double> &h) {
-    int rc = hip_check(c, hipMemcpyAsync(h.data(), src, sizeof(double) * h.size(), hipMemcpyDeviceToHost, c->stream),
-                       "copy to host");
-    if (rc) return rc;
-    return hip_check(c, hipStreamSynchronize(c->stream), "copy to host");
-}
-
 // Homogeneous strain of an applied stress for cubic C:
 // normal part eps = (sigma - c12 tr(sigma) / (c11 + 2 c12)) / (c11 - c12),
 // shear eps_ij = sigma_ij / (2 c44).
@@ -168,36 +154,119 @@ namespace gspm {
 
 // Caller-order n0 x 3 -> internal component-major 3 x n.  The copies of a
 // periodic node must agree to 1e-12 relative.
-int gather_user(gspm_ctx *c, const double *v, std::vector<double> &out) {
-    const int n = c->n;
-    out.assign(3 * static_cast<size_t>(n), 0.0);
-    std::vector<uint8_t> seen(static_cast<size_t>(n), 0);
-    for (int64_t i = 0; i < c->n0; ++i) {
-        const int32_t k = c->user2int[i];
-        for (int a = 0; a < 3; ++a) {
-            const double x = v[i * 3 + a];
-            if (!std::isfinite(x)) {
-                c->err = "non-finite value in a nodal field";
-                return GSPM_E_ARG;
-            }
-            double &dst = out[static_cast<size_t>(a) * n + k];
-            if (!seen[k]) dst = x;
-            else if (std::fabs(dst - x) > 1e-12 * std::max(std::fabs(dst), std::fabs(x))) {
-                c->err = "periodic copies of a node carry different values";
-                return GSPM_E_ARG;
-            }
+namespace {
+
+constexpr size_t kStageHalf = 1 << 20;
+
+// The pinned staging buffer.  Copies from and to the caller's pageable memory
+// take 250 us at 0.6 MB and 1.1 to 1.5 ms at 24 MB (the runtime pins the pages
+// or stages them); through here 40 us and 0.9 ms.  With the permutation on the
+// device (it took 3 ms a field on the host) a field of 1M nodes is set or read
+// in 1.1 ms instead of 5.7.  Without it (no pinned
+// memory left) the arrays are copied directly.
+void stage_setup(gspm_ctx *c) {
+    const size_t half = std::min(kStageHalf, (3 * sizeof(double) * static_cast<size_t>(c->n0) + 4095) / 4096 * 4096);
+    if (c->stage_half >= half) return;
+    if (c->stage) hipHostFree(c->stage);
+    c->stage = nullptr;
+    c->stage_half = 0;
+    for (hipEvent_t &e : c->stage_ev)
+        if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            e = nullptr;
+            (void)hipGetLastError();
+            return;
         }
-        seen[k] = 1;
+    if (hipHostMalloc(reinterpret_cast<void **>(&c->stage), 2 * half, hipHostMallocDefault) != hipSuccess) {
+        c->stage = nullptr;
+        (void)hipGetLastError();
+        return;
+    }
+    c->stage_half = half;
+}
+
+// dst (device) <- src: enqueued; a half is filled again once its copy is done.
+int to_device(gspm_ctx *c, void *dst, const void *src, size_t bytes) {
+    if (!c->stage) {
+        const int rc = hip_check(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream), "copy to device");
+        return rc ? rc : hip_check(c, hipStreamSynchronize(c->stream), "copy to device");
+    }
+    int h = 0;
+    for (size_t at = 0; at < bytes; at += c->stage_half, h ^= 1) {
+        const size_t len = std::min(c->stage_half, bytes - at);
+        char *buf = c->stage + h * c->stage_half;
+        hipError_t e = hipEventSynchronize(c->stage_ev[h]);
+        if (e == hipSuccess) {
+            std::memcpy(buf, static_cast<const char *>(src) + at, len);
+            e = hipMemcpyAsync(static_cast<char *>(dst) + at, buf, len, hipMemcpyHostToDevice, c->stream);
+        }
+        if (e == hipSuccess) e = hipEventRecord(c->stage_ev[h], c->stream);
+        if (e != hipSuccess) return hip_check(c, e, "copy to device");
     }
     return GSPM_OK;
 }
 
-void scatter_user(const gspm_ctx *c, const std::vector<double> &in, double *out) {
-    const int n = c->n;
-    for (int64_t i = 0; i < c->n0; ++i) {
-        const int32_t k = c->user2int[i];
-        for (int a = 0; a < 3; ++a) out[i * 3 + a] = in[static_cast<size_t>(a) * n + k];
+// dst <- src (device), finished on return; a half is copied out while the other fills.
+int to_host(gspm_ctx *c, void *dst, const void *src, size_t bytes) {
+    if (!c->stage) {
+        const int rc = hip_check(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream), "copy to host");
+        return rc ? rc : hip_check(c, hipStreamSynchronize(c->stream), "copy to host");
     }
+    const size_t half = c->stage_half, chunks = (bytes + half - 1) / half;
+    hipError_t e = hipSuccess;
+    for (size_t q = 0; q <= chunks && e == hipSuccess; ++q) {
+        if (q < chunks) {
+            const size_t len = std::min(half, bytes - q * half);
+            e = hipMemcpyAsync(c->stage + (q & 1) * half, static_cast<const char *>(src) + q * half, len,
+                               hipMemcpyDeviceToHost, c->stream);
+            if (e == hipSuccess) e = hipEventRecord(c->stage_ev[q & 1], c->stream);
+        }
+        if (q > 0 && e == hipSuccess) {
+            const size_t p = q - 1, len = std::min(half, bytes - p * half);
+            e = hipEventSynchronize(c->stage_ev[p & 1]);
+            if (e == hipSuccess) std::memcpy(static_cast<char *>(dst) + p * half, c->stage + (p & 1) * half, len);
+        }
+    }
+    return hip_check(c, e, "copy to host");
+}
+
+unsigned long long *user_report(gspm_ctx *c) { return reinterpret_cast<unsigned long long *>(c->h_step + 16); }
+
+UserMap user_map(gspm_ctx *c) {
+    return UserMap{c->n0, c->n, c->p0, c->d.user2int, c->d.rep, c->d.w, c->d.user, c->d.user_err, user_report(c)};
+}
+
+}  // namespace
+
+int user_put(gspm_ctx *c, const double *v, int nc, int kind, double *dst) {
+    const int rc = to_device(c, c->d.user, v, sizeof(double) * static_cast<size_t>(nc) * static_cast<size_t>(c->n0));
+    if (rc) {
+        c->user_seq = 0;
+        return rc;
+    }
+    if (c->user_seq == 0) *user_report(c) = kUserFine;
+    launch_user_put(user_map(c), nc, kind, c->user_seq++, dst, c->stream);
+    return GSPM_OK;
+}
+
+int user_done(gspm_ctx *c) {
+    c->user_seq = 0;
+    const int rc = hip_check(c, hipStreamSynchronize(c->stream), "copy to device");
+    if (rc) return rc;
+    const unsigned long long key = *user_report(c);
+    if (key == kUserFine) return GSPM_OK;
+    const unsigned long long fine = kUserFine;
+    hipMemcpyAsync(c->d.user_err, &fine, sizeof fine, hipMemcpyHostToDevice, c->stream);
+    const int rr = hip_check(c, hipStreamSynchronize(c->stream), "copy to device");
+    if (rr) return rr;
+    c->err = key & kUserZero       ? "set_field: zero magnetisation on a magnetic node"
+             : key & kUserMismatch ? "periodic copies of a node carry different values"
+                                   : "non-finite value in a nodal field";
+    return GSPM_E_ARG;
+}
+
+int user_get(gspm_ctx *c, const double *src, int nc, double *v) {
+    launch_user_get(user_map(c), nc, src, c->stream);
+    return to_host(c, v, c->d.user, sizeof(double) * static_cast<size_t>(nc) * static_cast<size_t>(c->n0));
 }
 
 }  // namespace gspm
@@ -217,6 +286,9 @@ gspm_ctx::~gspm_ctx() {
     if (h_flags) hipHostFree(h_flags);
     if (h_mixed) hipHostFree(h_mixed);
     if (h_step) hipHostFree(h_step);
+    if (stage) hipHostFree(stage);
+    for (hipEvent_t e : stage_ev)
+        if (e) hipEventDestroy(e);
     if (own_stream && stream) hipStreamDestroy(stream);
 }
 
@@ -240,6 +312,7 @@ void gspm_ctx::release_mesh() {
     dev_free(this, b.gcorr); dev_free(this, b.gstart);
     dev_free(this, b.mprev); dev_free(this, b.uprev); dev_free(this, b.du_prev); dev_free(this, b.kdu); dev_free(this, b.wred); dev_free(this, b.wcoef);
     dev_free(this, b.ud); dev_free(this, b.udnext); dev_free(this, b.rep);
+    dev_free(this, b.user2int); dev_free(this, b.user); dev_free(this, b.user_err);
     dev_free(this, b.cg_rz); dev_free(this, b.cgi_rz);
     dev_free(this, b.cg_rzq); dev_free(this, b.cg_qzq); dev_free(this, b.cgi_rzq); dev_free(this, b.cgi_qzq);
     dev_free(this, b.det_part); dev_free(this, b.det_dst); dev_free(this, b.det_count); dev_free(this, b.inc_ptr);
@@ -353,9 +426,9 @@ gspm_status gspm_create(gspm_ctx **out, const gspm_create_opts *opts) {
                             hipHostMallocCoherent) == hipSuccess;
     ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_mixed), sizeof(double) * 16 * kShards,
                              hipHostMallocCoherent) == hipSuccess;
-    ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_step), sizeof(double) * 16 + sizeof(ResResult),
+    ok = ok && hipHostMalloc(reinterpret_cast<void **>(&c->h_step), sizeof(double) * 32 + sizeof(ResResult),
                              hipHostMallocCoherent) == hipSuccess;
-    if (ok) c->h_res = reinterpret_cast<ResResult *>(c->h_step + 16);
+    if (ok) c->h_res = reinterpret_cast<ResResult *>(c->h_step + 32);
     for (auto &e : c->ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreate(&c->t0) == hipSuccess && hipEventCreate(&c->t1) == hipSuccess;
     for (auto &e : c->phase_ev) ok = ok && hipEventCreate(&e) == hipSuccess;
@@ -493,6 +566,9 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
         rc = rc ? rc : dev_alloc(c, &d.ud, n);
         rc = rc ? rc : dev_alloc(c, &d.udnext, n);
         rc = rc ? rc : dev_alloc(c, &d.rep, n);
+        rc = rc ? rc : dev_alloc(c, &d.user2int, static_cast<size_t>(hm.n0));
+        rc = rc ? rc : dev_alloc(c, &d.user, 3 * static_cast<size_t>(hm.n0));
+        rc = rc ? rc : dev_alloc(c, &d.user_err, 1);
         rc = rc ? rc : dev_alloc(c, &d.cg_rz, static_cast<size_t>(kMaxComp) * kRing * kShards);
         rc = rc ? rc : dev_alloc(c, &d.cg_rzq, static_cast<size_t>(kMaxComp) * kRing * kShards);
         rc = rc ? rc : dev_alloc(c, &d.cg_qzq, static_cast<size_t>(kMaxComp) * kRing * kShards);
@@ -624,6 +700,9 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
     std::vector<int32_t> rep(n, -1);
     for (int64_t i = hm.n0 - 1; i >= 0; --i) rep[static_cast<size_t>(hm.user2int[i])] = static_cast<int32_t>(i);
     hipMemcpyAsync(d.rep, rep.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s);
+    hipMemcpyAsync(d.user2int, hm.user2int.data(), sizeof(int32_t) * hm.user2int.size(), hipMemcpyHostToDevice, s);
+    const unsigned long long fine = kUserFine;
+    hipMemcpyAsync(d.user_err, &fine, sizeof fine, hipMemcpyHostToDevice, s);
     if (nseg) {
         hipMemcpyAsync(d.seg_ent, hm.seg_ent.data(), sizeof(uint16_t) * hm.seg_ent.size(), hipMemcpyHostToDevice, s);
         hipMemcpyAsync(d.seg_off, hm.seg_off.data(), sizeof(uint32_t) * nseg, hipMemcpyHostToDevice, s);
@@ -657,6 +736,7 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
     for (size_t q = 0; q < c->tets_int.size(); ++q) c->tets_int[q] = hm.user2int[tets[q]];
     c->user2int = std::move(hm.user2int);
     c->w_host = hm.w;
+    stage_setup(c);
     c->nmag = 0;
     for (double wv : c->w_host) c->nmag += wv > 0.0;
     auto &mv = c->mv;
@@ -829,43 +909,16 @@ gspm_status gspm_set_field(gspm_ctx *c, gspm_field which, const double *v, int64
     if (which != GSPM_FIELD_M && which != GSPM_FIELD_U && which != GSPM_FIELD_UD)
         return fail(c, GSPM_E_ARG, "set_field: unknown field");
     hipSetDevice(c->device);
-    std::vector<double> h;
-    if (which == GSPM_FIELD_UD) {
-        // one value per node: spread into the first column of the n0 x 3 layout
-        std::vector<double> v3(3 * static_cast<size_t>(c->n0), 0.0);
-        for (int64_t i = 0; i < c->n0; ++i) v3[3 * i] = v[i];
-        int rc = gather_user(c, v3.data(), h);
-        if (rc) return static_cast<gspm_status>(rc);
-        h.resize(static_cast<size_t>(c->n));
-        return static_cast<gspm_status>(upload(c, c->d.ud, h));
-    }
-    int rc = gather_user(c, v, h);
+    const bool is_m = which == GSPM_FIELD_M, scalar = which == GSPM_FIELD_UD;
+    int rc = user_put(c, v, scalar ? 1 : 3, is_m ? USER_M : USER_ALL, scalar ? c->d.ud : is_m ? c->d.m : c->d.u);
+    rc = rc ? rc : user_done(c);
     if (rc) return static_cast<gspm_status>(rc);
-    const int n = c->n;
-    if (which == GSPM_FIELD_M) {
-        for (int k = 0; k < n; ++k) {
-            double *a = &h[k], *b = &h[static_cast<size_t>(n) + k], *cc = &h[2 * static_cast<size_t>(n) + k];
-            if (!(c->w_host[k] > 0.0)) {
-                *a = *b = *cc = 0.0;
-                continue;
-            }
-            const double r = std::sqrt(*a * *a + *b * *b + *cc * *cc);
-            if (!(r > 0.0)) return fail(c, GSPM_E_ARG, "set_field: zero magnetisation on a magnetic node");
-            // a vector of unit length to rounding (a state read back with get_field) is kept bit for bit,
-            // so a saved state restores exactly
-            if (std::fabs(r - 1.0) > 1e-14) {
-                *a /= r; *b /= r; *cc /= r;
-            }
-        }
-        rc = upload(c, c->d.m, h);
-        if (rc) return static_cast<gspm_status>(rc);
+    if (is_m) {
         c->have_m = true;
         c->have_prev = false;     // a new state has no history for the warm starts
         c->gcorr_ok = 0;
         c->commits = 0;
-    } else {
-        rc = upload(c, c->d.u, h);
-        if (rc) return static_cast<gspm_status>(rc);
+    } else if (!scalar) {
         c->commits = 0;           // u^{n-2} no longer precedes u
     }
     return GSPM_OK;
@@ -879,18 +932,8 @@ gspm_status gspm_get_field(gspm_ctx *c, gspm_field which, double *out, int64_t n
     if (which != GSPM_FIELD_M && which != GSPM_FIELD_U && which != GSPM_FIELD_UD)
         return fail(c, GSPM_E_ARG, "get_field: unknown field");
     hipSetDevice(c->device);
-    if (which == GSPM_FIELD_UD) {
-        std::vector<double> h(static_cast<size_t>(c->n));
-        int rc = download(c, c->d.ud, h);
-        if (rc) return static_cast<gspm_status>(rc);
-        for (int64_t i = 0; i < c->n0; ++i) out[i] = h[static_cast<size_t>(c->user2int[i])];
-        return GSPM_OK;
-    }
-    std::vector<double> h(3 * static_cast<size_t>(c->n));
-    int rc = download(c, which == GSPM_FIELD_M ? c->d.m : c->d.u, h);
-    if (rc) return static_cast<gspm_status>(rc);
-    scatter_user(c, h, out);
-    return GSPM_OK;
+    const double *src = which == GSPM_FIELD_M ? c->d.m : which == GSPM_FIELD_U ? c->d.u : c->d.ud;
+    return static_cast<gspm_status>(user_get(c, src, which == GSPM_FIELD_UD ? 1 : 3, out));
 }
 
 gspm_status gspm_step(gspm_ctx *c, double dt, int32_t n_steps, gspm_step_stats *stats) {
@@ -1011,10 +1054,8 @@ gspm_status gspm_apply(gspm_ctx *c, gspm_op op, double eps, const double *x, dou
         return fail(c, GSPM_E_STATE, "apply(PRECOND) needs elastic_precond = GSPM_PRECOND_GREEN on an FP64 context");
     if (!std::isfinite(eps)) return fail(c, GSPM_E_ARG, "apply: non-finite eps");
     hipSetDevice(c->device);
-    std::vector<double> h;
-    int rc = gather_user(c, x, h);
-    if (rc) return static_cast<gspm_status>(rc);
-    rc = upload(c, c->d.ms, h);
+    int rc = user_put(c, x, 3, USER_ALL, c->d.ms);
+    rc = rc ? rc : user_done(c);
     if (rc) return static_cast<gspm_status>(rc);
     if (op == GSPM_OP_PRECOND) {
         rc = green_apply64(c, c->d.ms, c->d.q);
@@ -1031,10 +1072,7 @@ gspm_status gspm_apply(gspm_ctx *c, gspm_op op, double eps, const double *x, dou
         launch_gs_rows<double>(c->mv_rows, gs_rows(c, e, mass, false), 3, MV_APPLY, c->d.ms, c->d.q, nullptr, nullptr,
                                c->cg, c->stream);
     }
-    rc = download(c, c->d.q, h);
-    if (rc) return static_cast<gspm_status>(rc);
-    scatter_user(c, h, y);
-    return GSPM_OK;
+    return static_cast<gspm_status>(user_get(c, c->d.q, 3, y));
 }
 
 gspm_status gspm_solve(gspm_ctx *c, gspm_op op, double eps, const double *b, double *x, int64_t n_nodes, double tol,
@@ -1048,35 +1086,24 @@ gspm_status gspm_solve(gspm_ctx *c, gspm_op op, double eps, const double *b, dou
     if (op == GSPM_OP_ELASTIC && !c->have_params) return fail(c, GSPM_E_STATE, "solve(ELASTIC) needs set_params");
     if (!(tol > 0) || maxit <= 0 || !std::isfinite(eps)) return fail(c, GSPM_E_ARG, "solve: tol and maxit must be positive");
     hipSetDevice(c->device);
-    std::vector<double> hb, hx;
-    int rc = gather_user(c, b, hb);
-    if (!rc) rc = gather_user(c, x, hx);
-    if (rc) return static_cast<gspm_status>(rc);
     const int n = c->n;
     const bool el = op == GSPM_OP_ELASTIC, msop = op == GSPM_OP_MS;
     const int ns = el ? 1 : 3;
     const bool green = el && c->p.elastic_precond == GSPM_PRECOND_GREEN;
-    for (int k = 0; k < n; ++k) {
-        if (green) break;              // the periodic system: nothing pinned before the solve
-        const bool fixed = (el || msop) ? (k == c->p0) : !(c->w_host[k] > 0.0);
-        if (!fixed) continue;
-        for (int a = 0; a < 3; ++a) hb[static_cast<size_t>(a) * n + k] = hx[static_cast<size_t>(a) * n + k] = 0.0;
-    }
-    std::vector<double> bbh(static_cast<size_t>(kMaxComp) * kShards, 0.0);
-    for (int a = 0; a < 3; ++a)
-        for (int k = 0; k < n; ++k) bbh[static_cast<size_t>(el ? 0 : a) * kShards] += hb[static_cast<size_t>(a) * n + k] * hb[static_cast<size_t>(a) * n + k];
-    cg_prepare(c, ns);
-    hipMemcpyAsync(c->d.cg_bb, bbh.data(), sizeof(double) * bbh.size(), hipMemcpyHostToDevice, c->stream);
-    rc = upload(c, c->d.b, hb);
-    if (!rc) rc = upload(c, c->d.mnext, hx);
+    // preconditioned, the periodic system: nothing pinned before the solve
+    const int kind = green ? USER_ALL : el || msop ? USER_PINNED : USER_MAGNETIC;
+    int rc = user_put(c, b, 3, kind, c->d.b);
+    rc = rc ? rc : user_put(c, x, 3, kind, c->d.mnext);
+    rc = rc ? rc : user_done(c);
     if (rc) return static_cast<gspm_status>(rc);
+    cg_prepare(c, ns);
+    launch_square_sums(ns, (el ? 3 : 1) * static_cast<int64_t>(n), c->d.b, c->d.cg_bb, c->stream);
     CgResult r = el ? cg_elastic(c, c->d.mnext, c->d.b, tol, maxit, SK_OTHER)
                  : msop ? cg_ms(c, 3, c->d.mnext, c->d.b, tol, maxit, SK_OTHER)
                         : cg_gs(c, 3, eps, c->d.mnext, c->d.b, tol, maxit, SK_OTHER);
     if (iters) *iters = r.iters[0] + r.iters[1] + r.iters[2];
-    rc = download(c, c->d.mnext, hx);
+    rc = user_get(c, c->d.mnext, 3, x);
     if (rc) return static_cast<gspm_status>(rc);
-    scatter_user(c, hx, x);
     return static_cast<gspm_status>(r.status);
 }
 

@@ -286,6 +286,27 @@ void launch_elastic_pcg(const MeshView &mv, const Material &mat, int k, const T 
 // ---------------------------------------------------------------- launchers
 
 void launch_fill(double *p, int64_t n, double v, hipStream_t s);
+
+// The caller's node order on the device: v is a staging copy of the caller's
+// node-major array (n0 x 3 or n0 x 1), err the least key of a failed check.
+struct UserMap {
+    int64_t n0;
+    int32_t n, p0;
+    const int32_t *user2int, *rep;
+    const double *w;
+    double *v;
+    unsigned long long *err, *report;   // device; pinned host
+};
+// What put does with some nodes: nothing; normalise M and clear it off the
+// magnetic nodes; clear the pinned node; clear off the magnetic nodes.
+enum UserKind { USER_ALL = 0, USER_M = 1, USER_PINNED = 2, USER_MAGNETIC = 3 };
+// Keys order failures as a check in caller order would meet them: by array, then
+// values by node and component (bit 0: a copy that differs), then zero vectors.
+constexpr uint64_t kUserFine = ~uint64_t(0), kUserMismatch = 1, kUserZero = uint64_t(1) << 57;
+constexpr int kUserSeqShift = 58;
+void launch_user_put(const UserMap &u, int nc, int kind, int seq, double *dst, hipStream_t s);
+void launch_user_get(const UserMap &u, int nc, const double *src, hipStream_t s);
+void launch_square_sums(int ns, int64_t count, const double *x, double *out, hipStream_t s);
 void launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 
 // The corrected start of a GS solve: x0 += corr (when use) and start = x0;

@@ -58,6 +58,9 @@ struct DeviceBuffers {
     double *wcoef = nullptr;      // 2: coefficients of the last minimum-residual start
     double *ud = nullptr, *udnext = nullptr;   // n: local magnetostatic potential (committed, in progress)
     int32_t *rep = nullptr;       // n: the first caller node of each unique node
+    int32_t *user2int = nullptr;  // n0: the unique node of each caller node
+    double *user = nullptr;       // 3 n0: a caller array
+    unsigned long long *user_err = nullptr;
     double *cg_rz = nullptr, *cgi_rz = nullptr;   // r . D^-1 r rings of the Jacobi-preconditioned GS solves
     double *cg_rzq = nullptr, *cg_qzq = nullptr, *cgi_rzq = nullptr, *cgi_qzq = nullptr;   // r.D^-1 q, q.D^-1 q rings
     // deterministic mode: the fixed-order sums' slots and per owned node its element copies (MeshView)
@@ -171,6 +174,10 @@ struct gspm_ctx {
     double vc = 0.0;
     double box_lo[3] = {0.0, 0.0, 0.0};   // the periodic box's min corner
     std::vector<int32_t> user2int;
+    char *stage = nullptr;                // pinned: two halves through which caller arrays pass
+    size_t stage_half = 0;
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};
+    int user_seq = 0;                     // arrays put since the last user_done
     std::vector<double> w_host;   // lumped weights (internal order)
 
     gspm::DeviceBuffers d;
@@ -290,8 +297,12 @@ void ctx_free(const gspm_ctx *c, void *p);
 // coefficients minimising |b - K x| (stored at d.wcoef).  Leaves the CG scalars as
 // cg_prepare set them.
 int minres_start(gspm_ctx *c, const double *m, const double *mprev, const double *uprev, double *x, const double *b);
-// Caller-order n0 x 3 <-> internal component-major 3 x n (api.cpp).
-int gather_user(gspm_ctx *c, const double *v, std::vector<double> &out);
-void scatter_user(const gspm_ctx *c, const std::vector<double> &in, double *out);
+// Caller-order n0 x nc <-> internal component-major (api.cpp).  user_put checks
+// the array (UserKind) and enqueues its way to dst; user_done waits and reports
+// the first failure of the arrays put since the last.  user_get returns with
+// the array filled.
+int user_put(gspm_ctx *c, const double *v, int nc, int kind, double *dst);
+int user_done(gspm_ctx *c);
+int user_get(gspm_ctx *c, const double *src, int nc, double *v);
 
 }  // namespace gspm

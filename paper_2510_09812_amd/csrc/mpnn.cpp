@@ -149,16 +149,6 @@ using namespace gspm;
 
 namespace {
 
-// Caller-order fields -> internal device vectors (via the context's gather).
-int upload_user(gspm_ctx *c, const double *v, double *dst) {
-    std::vector<double> h;
-    int rc = gather_user(c, v, h);
-    if (rc) return rc;
-    rc = hip_check(c, hipMemcpyAsync(dst, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, c->stream),
-                   "copy to device");
-    return rc ? rc : hip_check(c, hipStreamSynchronize(c->stream), "copy to device");
-}
-
 gspm_status nn_ready(gspm_ctx *c) {
     if (!c->have_mesh) return nfail(c, GSPM_E_STATE, "network call before upload_mesh");
     if (!c->nn.have_params) return nfail(c, GSPM_E_STATE, "network call before gspm_mpnn_set_params");
@@ -222,8 +212,9 @@ gspm_status gspm_mpnn_forward(gspm_ctx *c, const double *m_prev, const double *m
     if (n_nodes != c->n0) return nfail(c, GSPM_E_ARG, "mpnn_forward: n_nodes differs from the mesh");
     hipSetDevice(c->device);
     auto &nn = c->nn;
-    int rc = upload_user(c, m_prev, nn.mp_in);
-    rc = rc ? rc : upload_user(c, m, nn.m_in);
+    int rc = user_put(c, m_prev, 3, USER_ALL, nn.mp_in);
+    rc = rc ? rc : user_put(c, m, 3, USER_ALL, nn.m_in);
+    rc = rc ? rc : user_done(c);
     if (rc) return static_cast<gspm_status>(rc);
     mpnn::launch_forward(nn.graph, c->mv, nn.net, nn.m_in, nn.mp_in, nn.red, nn.A, c->mat.l100, nullptr, c->stream);
     const size_t n = static_cast<size_t>(c->n);
@@ -259,9 +250,10 @@ gspm_status gspm_mpnn_train_step(gspm_ctx *c, const double *m_prev, const double
     if (n_nodes != c->n0) return nfail(c, GSPM_E_ARG, "mpnn_train_step: n_nodes differs from the mesh");
     hipSetDevice(c->device);
     auto &nn = c->nn;
-    int rc = upload_user(c, m_prev, nn.mp_in);
-    rc = rc ? rc : upload_user(c, m, nn.m_in);
-    rc = rc ? rc : upload_user(c, du, nn.du);
+    int rc = user_put(c, m_prev, 3, USER_ALL, nn.mp_in);
+    rc = rc ? rc : user_put(c, m, 3, USER_ALL, nn.m_in);
+    rc = rc ? rc : user_put(c, du, 3, USER_ALL, nn.du);
+    rc = rc ? rc : user_done(c);
     if (rc) return static_cast<gspm_status>(rc);
     hipStream_t s = c->stream;
     mpnn::launch_forward(nn.graph, c->mv, nn.net, nn.m_in, nn.mp_in, nn.red, nn.A, c->mat.l100, nullptr, s);
@@ -296,8 +288,9 @@ gspm_status gspm_mpnn_warm_start(gspm_ctx *c, const double *m_prev, const double
     hipSetDevice(c->device);
     auto &nn = c->nn;
     auto &d = c->d;
-    int rc = upload_user(c, m_prev, nn.mp_in);
-    if (!rc && u_prev) rc = upload_user(c, u_prev, nn.du);
+    int rc = user_put(c, m_prev, 3, USER_ALL, nn.mp_in);
+    if (!rc && u_prev) rc = user_put(c, u_prev, 3, USER_ALL, nn.du);
+    rc = rc ? rc : user_done(c);
     if (rc) return static_cast<gspm_status>(rc);
     hipStream_t s = c->stream;
     const size_t bytes3 = sizeof(double) * 3 * static_cast<size_t>(c->n);
@@ -315,13 +308,11 @@ gspm_status gspm_mpnn_warm_start(gspm_ctx *c, const double *m_prev, const double
                            hipMemcpyHostToDevice, s);
     }
     minres_start(c, d.m, nn.mp_in, u_prev ? nn.du : nullptr, d.unext, d.b);
-    std::vector<double> h(3 * static_cast<size_t>(c->n));
     double ch[2] = {0.0, 0.0};
-    hipMemcpyAsync(h.data(), d.unext, bytes3, hipMemcpyDeviceToHost, s);
     hipMemcpyAsync(ch, d.wcoef, sizeof ch, hipMemcpyDeviceToHost, s);
     rc = hip_check(c, hipStreamSynchronize(s), "mpnn_warm_start");
+    rc = rc ? rc : user_get(c, d.unext, 3, u0);
     if (rc) return static_cast<gspm_status>(rc);
-    scatter_user(c, h, u0);
     if (coef) {
         coef[0] = ch[0];
         coef[1] = ch[1];

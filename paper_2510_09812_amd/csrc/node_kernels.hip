@@ -697,6 +697,126 @@ void launch_normalize(int n, const double *w, const double *mss, const double *m
     launch_det_finish(det, s);
 }
 
+// ------------------------------------------------------------ caller arrays
+
+// |x| (of the first three), each operation rounded by itself.
+template <int NC>
+__device__ __forceinline__ double length3(const double (&x)[NC]) {
+#pragma clang fp contract(off)
+    return sqrt(x[0] * x[0] + x[NC > 1] * x[NC > 1] + x[NC > 2 ? 2 : 0] * x[NC > 2 ? 2 : 0]);
+}
+
+// Checks the caller's node-major array v (n0 x NC): every value finite, the
+// periodic copies of a node equal to its first to 1e-12, and, for M, no zero
+// vector on a magnetic node.  The least of the keys of what fails goes to *err
+// (UserKey), so that the report does not depend on the order of the threads.
+template <int NC>
+__global__ void __launch_bounds__(kThreads) k_user_check(int64_t n0, const int32_t *user2int, const int32_t *rep,
+                                                         const double *w, const double *v, int kind, uint64_t key0,
+                                                         unsigned long long *err) {
+    for (int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; i < n0;
+         i += static_cast<int64_t>(gridDim.x) * kThreads) {
+        const int32_t k = user2int[i], f = rep[k];
+        double x[NC];
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            x[a] = v[i * NC + a];
+            const uint64_t key = key0 | static_cast<uint64_t>((i * 3 + a) * 2);
+            if (!__builtin_isfinite(x[a])) {
+                atomicMin(err, static_cast<unsigned long long>(key));
+            } else if (f != i) {
+                const double d = v[static_cast<int64_t>(f) * NC + a];
+                if (fabs(d - x[a]) > 1e-12 * fmax(fabs(d), fabs(x[a])))
+                    atomicMin(err, static_cast<unsigned long long>(key | kUserMismatch));
+            }
+        }
+        if (NC == 3 && kind == USER_M && f == i && w[k] > 0.0 && !(length3(x) > 0.0))
+            atomicMin(err, static_cast<unsigned long long>(key0 | kUserZero));
+    }
+}
+
+// The checked array in internal order, component-major; nothing is written
+// once a check has failed.  `report` (pinned) receives *err.
+template <int NC>
+__global__ void __launch_bounds__(kThreads) k_user_put(int n, int p0, const int32_t *rep, const double *w,
+                                                       const double *v, int kind, const unsigned long long *err,
+                                                       double *dst, unsigned long long *report) {
+    const unsigned long long e = *err;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *report = e;
+    if (e != kUserFine) return;
+    for (int k = blockIdx.x * kThreads + threadIdx.x; k < n; k += gridDim.x * kThreads) {
+        double x[NC];
+#pragma unroll
+        for (int a = 0; a < NC; ++a) x[a] = v[static_cast<int64_t>(rep[k]) * NC + a];
+        const bool zero = kind == USER_M || kind == USER_MAGNETIC ? !(w[k] > 0.0) : kind == USER_PINNED && k == p0;
+        if (NC == 3 && kind == USER_M && !zero) {
+            const double r = length3(x);
+            // a vector of unit length to rounding (a state read back) is kept bit for bit, so a saved state
+            // restores exactly
+            if (fabs(r - 1.0) > 1e-14) {
+#pragma unroll
+                for (int a = 0; a < NC; ++a) x[a] /= r;
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < NC; ++a) dst[static_cast<size_t>(a) * n + k] = zero ? 0.0 : x[a];
+    }
+}
+
+template <int NC>
+__global__ void __launch_bounds__(kThreads) k_user_get(int64_t n0, int n, const int32_t *user2int, const double *src,
+                                                       double *v) {
+    for (int64_t q = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; q < NC * n0;
+         q += static_cast<int64_t>(gridDim.x) * kThreads) {
+        const int64_t i = q / NC;
+        const int a = static_cast<int>(q - i * NC);
+        v[q] = src[static_cast<size_t>(a) * n + user2int[i]];
+    }
+}
+
+void launch_user_put(const UserMap &u, int nc, int kind, int seq, double *dst, hipStream_t s) {
+    const uint64_t key0 = static_cast<uint64_t>(seq) << kUserSeqShift;
+    const dim3 gc(node_grid(u.n0)), gp(node_grid(u.n)), t(kThreads);
+    if (nc == 3) {
+        hipLaunchKernelGGL(k_user_check<3>, gc, t, 0, s, u.n0, u.user2int, u.rep, u.w, u.v, kind, key0, u.err);
+        hipLaunchKernelGGL(k_user_put<3>, gp, t, 0, s, u.n, u.p0, u.rep, u.w, u.v, kind, u.err, dst, u.report);
+    } else {
+        hipLaunchKernelGGL(k_user_check<1>, gc, t, 0, s, u.n0, u.user2int, u.rep, u.w, u.v, kind, key0, u.err);
+        hipLaunchKernelGGL(k_user_put<1>, gp, t, 0, s, u.n, u.p0, u.rep, u.w, u.v, kind, u.err, dst, u.report);
+    }
+}
+
+void launch_user_get(const UserMap &u, int nc, const double *src, hipStream_t s) {
+    const dim3 g(node_grid(nc * u.n0)), t(kThreads);
+    if (nc == 3)
+        hipLaunchKernelGGL(k_user_get<3>, g, t, 0, s, u.n0, u.n, u.user2int, src, u.v);
+    else
+        hipLaunchKernelGGL(k_user_get<1>, g, t, 0, s, u.n0, u.n, u.user2int, src, u.v);
+}
+
+// out[c * kShards] = sum of squares of the c-th `count` values, the other shards 0: a workgroup each, in a fixed order.
+__global__ void __launch_bounds__(1024) k_square_sums(int64_t count, const double *x, double *out) {
+    __shared__ double red[16];
+    const double *v = x + blockIdx.x * count;
+    double acc = 0.0;
+    for (int64_t i = threadIdx.x; i < count; i += 1024) acc += v[i] * v[i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x < kShards) {
+        double t = 0.0;
+        if (threadIdx.x == 0)
+            for (int q = 0; q < 16; ++q) t += red[q];
+        out[blockIdx.x * kShards + threadIdx.x] = t;
+    }
+}
+
+void launch_square_sums(int ns, int64_t count, const double *x, double *out, hipStream_t s) {
+    static_assert(kShards <= 1024, "a thread a shard");
+    hipLaunchKernelGGL(k_square_sums, dim3(ns), dim3(1024), 0, s, count, x, out);
+}
+
 // ------------------------------------------------------- deterministic sums
 
 // The recorded sums of the last producer launch: each sum's workgroup slots
