@@ -11,9 +11,7 @@ namespace gspm {
 
 constexpr int kResThreads = 512;
 constexpr int kResMaxGroups = 256;     // workgroups of a launch, at most one per CU
-constexpr int kFlatGroups = 64;        // up to here every workgroup reads every other's sums
-constexpr int kGroup = 16;             // beyond, groups of this many are summed by a leader first
-constexpr int kMaxSlots = 64;          // sums a workgroup reads at once
+constexpr int kGroup = 16;             // workgroups that read each other's sums, and that a leader sums beyond
 constexpr int kSlotSums = 16;          // sums per slot, 16 bytes each
 constexpr int kResChunks = 3;          // 16-byte chunks per exchanged node: three doubles
 constexpr double kResInnerFloor = 1e-6;

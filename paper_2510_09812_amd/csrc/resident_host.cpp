@@ -28,16 +28,17 @@ void for_each_part(int32_t n, Body body) {
 
 }  // namespace
 
-// One workgroup per CU at most; up to kFlatGroups of them exchange their sums
-// in one hop (2.3 us an exchange in a probe, 3 us through leaders), so small
-// meshes stop there as long as that leaves a workgroup 256 rows at most, two
-// lanes for each.
+// One workgroup per CU at most, as many as have 64 rows: lanes per row count
+// for more than the second hop of the sums (FP64 elastic iterations: 9261 nodes
+// 4.9 us with 64 rows, eight lanes each, and 7.4 with 192, two each).  kGroup of
+// them need one hop, and small meshes stop there as long as that leaves a
+// workgroup 128 rows, four lanes each (1728 nodes: 4.2 us against 4.5).
 int32_t resident_rows(int32_t n, int32_t cus) {
     const int32_t most = std::min(cus, kResMaxGroups);
     if (most <= 0) return 0;
     const int32_t need = (n + most - 1) / most;
     int32_t nbr = std::max(64, (need + 63) / 64 * 64);
-    if (n <= kFlatGroups * 256) nbr = std::max(nbr, (((n + kFlatGroups - 1) / kFlatGroups) + 63) / 64 * 64);
+    if (n <= kGroup * 128) nbr = std::max(nbr, (((n + kGroup - 1) / kGroup) + 63) / 64 * 64);
     return nbr <= 4096 ? nbr : 0;
 }
 

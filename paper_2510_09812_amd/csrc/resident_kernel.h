@@ -10,10 +10,11 @@
 // registers, p of its rows and of their halo columns in LDS, and so do the
 // rows' coefficients where a thread has one row (beyond, they stream from L2
 // and Infinity Cache).  GS iteration on three components, launch-per-iteration
-// form against this one: 11.8 -> 4.0 us (729 nodes, FP64; without the gaps
-// between launches), 16.2 -> 7.6 us (97k nodes, FP64), 20.6 -> 6.5 us (97k,
-// FP32), 51 -> 33 us (970k, FP32, bound by the rows' stream of 84 MB); a mixed
-// solve also loses the host's turn in each refinement.
+// form (without the gaps between launches) against a whole solve here over its
+// iterations: 11.8 -> 5.8 us (729 nodes, FP64), 16.2 -> 6.8 us (97k nodes,
+// FP64), 20.6 -> 6.9 us (97k, FP32), 51 -> 35 us (970k, FP32, bound by the
+// rows' stream of 84 MB); a mixed solve also loses the host's turn in each
+// refinement.
 //
 // The halo keeps its own r and p: every workgroup applies the same alpha and
 // beta to the halo values it staged, so an iteration exchanges q alone, and q
@@ -28,9 +29,13 @@
 // cache flush is needed (across the XCDs' separate L2s neither).  Words
 // alternate between two buffers: a workgroup writes round t + 2 only after it
 // has all of round t + 1, which the others write after reading round t.  Up to
-// kFlatGroups workgroups read each other's sums directly; more of them go
-// through leaders of kGroup workgroups (all-to-all over 256 workgroups took
-// 6.8 us per exchange in a probe, two hops over groups of 16 about 3).
+// kGroup workgroups read each other's sums directly; more of them go through
+// leaders of kGroup workgroups (all-to-all over 256 workgroups took 6.8 us per
+// exchange in a probe, two hops over groups of 16 about 3).  One wave sums
+// either hop's slots straight from its loads, and a leader does so before it
+// waits for its halo: with the slots polled by all, summed through LDS behind
+// two barriers, and the leader's halo first, an elastic iteration of 97k nodes
+// took 6.2 us in FP32 and 9.0 in FP64 instead of 5.7 and 8.4.
 // All totals are added in a fixed order, the same in every workgroup, so all
 // take the same decisions, and results repeat bitwise.
 //
@@ -320,7 +325,9 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     constexpr int E = resident_entries(sizeof(T) == 4, BLK, L, RPT);
     // further entries of FP64 block rows in LDS, as many as fit (see resident_fits); the rest streams
     constexpr bool kLdsRows = BLK && sizeof(T) == 8 && RPT == 1 && L <= 2;
-    constexpr int kAhead = 5;
+    // (fetched ahead with one lane a row, five; with two lanes registers and LDS hold a Kuhn mesh's rows, and loading
+    // padding took an iteration of 39k nodes from 5.9 to 8.1 us)
+    constexpr int kAhead = kLdsRows && L == 1 ? 5 : 0;
     constexpr int kBuf = RPT > 1 ? 2 : 1;
     using V = Vec<T, NC>;
     // components of x staged at once for an FP64 residual: all, but at eight FP32 rows per thread two (LDS)
@@ -330,7 +337,9 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     __shared__ double s_part[kTh / 64][NV];
     __shared__ double s_tot[NV];
     __shared__ double s_al[NS], s_be[NS], s_bb[NS];
-    __shared__ int s_bad, s_end;
+    // a wait ran out: before the round's last barrier (stable from there to the next exchange), or in the halo beyond
+    // kHB nodes a thread, after it (seen a round later)
+    __shared__ int s_bad, s_late, s_end;
     const ResLayout &ly = a.ly;
     const int tid = threadIdx.x, n = ly.n, G = ly.G;
     const int wg = xcd_block(blockIdx.x, G);
@@ -347,9 +356,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         asm volatile("" : "+v"(v));
         return v;
     };
-    // LDS: slot words (as doubles once complete) | staging (p in T, or x in FP64) | halo r | halo 1/D
-    double *s_slot = reinterpret_cast<double *>(smem);
-    unsigned char *st = smem + sizeof(double) * kMaxSlots * NV;
+    // LDS: staging (p in T, or x in FP64) | halo r | halo 1/D | coefficients
+    unsigned char *st = smem;
     V *f = reinterpret_cast<V *>(st);
     X *fx = reinterpret_cast<X *>(st);
     T *hr = reinterpret_cast<T *>(st + a.stage_bytes);
@@ -357,7 +365,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     T *sk = hd + ((nhalo + 1) & ~1);               // [entry][6][lane] coefficients, then [entry][lane] columns
     uint16_t *sc_col = reinterpret_cast<uint16_t *>(sk + 6 * static_cast<size_t>(a.lds_entries) * a.lds_threads);
     const T *A = static_cast<const T *>(a.a), *D = static_cast<const T *>(a.d);
-    if (tid == 0) s_bad = s_end = 0;
+    if (tid == 0) s_bad = s_late = s_end = 0;
     uint32_t xt = a.epoch[0], rt = a.epoch[1];
 
     // export slots of the first halo nodes of this thread and of its rows, 1 / D of rows and halo
@@ -418,7 +426,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             __builtin_amdgcn_raw_buffer_store_b128(W::pack(v, j, xt), xq, xq_at(j, slot), 0, kAgent);
     };
     // B halo nodes' values of this round, all loads in flight; waits for them (slot < 0: none)
-    auto fetch = [&](const auto &slot, auto &v) {
+    auto fetch = [&](const auto &slot, auto &v, int &bad) {
         constexpr int B = sizeof(slot) / sizeof(slot[0]);
         using W = Wire<std::remove_cv_t<std::remove_reference_t<decltype(v[0][0])>>, NC>;
         u32x4 w[B][W::kChunks];
@@ -438,7 +446,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                     for (int j = 0; j < W::kChunks; ++j) ok &= w[u][j][1] == xt && w[u][j][3] == xt;
             if (ok) break;
             if (spin.over()) {
-                s_bad = 1;
+                bad = 1;
                 break;
             }
             asm volatile("" ::: "memory");         // the next pass reads again
@@ -451,25 +459,51 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 for (int c = 0; c < NC; ++c) v[u][c] = 0;
         }
     };
-    // `count` slots of NV sums, from slot `first` of the buffer on, into s_slot
+    // the workgroups' slots of NV sums, and the leaders'
     const __amdgpu_buffer_rsrc_t sums = __builtin_amdgcn_make_buffer_rsrc(
         a.slots, 0, static_cast<int>(resident_slot_bytes()), 0x00027000);
-    auto poll_slots = [&](int first, int count) {
-        constexpr int B = 2;
-        for (int i0 = tid; i0 < count * NV; i0 += B * kTh) {
-            u32x4 w[B];
+    auto put_sum = [&](int slot, int v, double t) {
+        const u64 b = static_cast<u64>(__double_as_longlong(t));
+        __builtin_amdgcn_raw_buffer_store_b128(
+            u32x4{static_cast<uint32_t>(b), rt, static_cast<uint32_t>(b >> 32), rt}, sums, (slot * kSlotSums + v) * 16, 0, kAgent);
+    };
+    // The totals of value sl >> 2 (four lanes of one wave a value, in a fixed order) into s_tot,
+    // and alpha and beta of the sets, by the lanes of sums 0 to NS - 1 (meaningful after an iteration's sums only).
+    // (few workgroups have few halo nodes: the last wave has none and polls while the first wait for theirs; at 729
+    // nodes 3.4 us an iteration against 3.7.  Beyond, every wave has some, and the first is 2 % the faster)
+    const bool summer = tid >> 6 == (G <= kGroup ? kTh / 64 - 1 : 0);
+    const int sl = tid & 63;
+    static_assert(4 * NV <= 64, "four lanes per value");
+    auto totals = [&](double t) {
+        const int v = sl >> 2, part = sl & 3;
+        if (part == 0 && v < NV) s_tot[v] = t;
+        const double rr2 = __shfl(t, 4 * (2 * NS) + sl, 64), rzq = __shfl(t, 4 * (3 * NS) + sl, 64),
+                     qzq = __shfl(t, 4 * (4 * NS) + sl, 64);
+        if (part == 0 && v < NS) {
+            const double alpha = rr2 / t, est = rr2 - 2.0 * alpha * rzq + alpha * alpha * qzq;
+            s_al[v] = alpha;
+            s_be[v] = (est > 0.0 ? est : 0.0) / rr2;
+        }
+        if (sl == 0) s_end = s_late;
+    };
+    // the sum of up to kGroup slots, by that wave alone and straight from the loads
+    auto wave_slots = [&](int first, int count) -> double {
+        static_assert(kGroup == 16, "four slots a lane");
+        const int v = sl >> 2, part = sl & 3;
+        u32x4 w[4];
+        double t = 0.0;
+        if (v < NV) {
             Spin spin;
             for (;;) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (part + 4 * u < count)
+                        w[u] = __builtin_amdgcn_raw_buffer_load_b128(
+                            sums, ((first + part + 4 * u) * kSlotSums + v) * 16, 0, kAgent);
                 bool ok = true;
 #pragma unroll
-                for (int u = 0; u < B; ++u) {
-                    const int i = i0 + u * kTh, s = i / NV, v = i - s * NV;
-                    if (i < count * NV)
-                        w[u] = __builtin_amdgcn_raw_buffer_load_b128(sums, ((first + s) * kSlotSums + v) * 16, 0, kAgent);
-                }
-#pragma unroll
-                for (int u = 0; u < B; ++u)
-                    if (i0 + u * kTh < count * NV) ok &= w[u][1] == rt && w[u][3] == rt;
+                for (int u = 0; u < 4; ++u)
+                    if (part + 4 * u < count) ok &= w[u][1] == rt && w[u][3] == rt;
                 if (ok) break;
                 if (spin.over()) {
                     s_bad = 1;
@@ -478,40 +512,13 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 asm volatile("" ::: "memory");     // the next pass reads again
             }
 #pragma unroll
-            for (int u = 0; u < B; ++u)
-                if (i0 + u * kTh < count * NV)
-                    s_slot[i0 + u * kTh] =
-                        __longlong_as_double(static_cast<long long>(w[u][0] | (static_cast<u64>(w[u][2]) << 32)));
+            for (int u = 0; u < 4; ++u)
+                if (part + 4 * u < count)
+                    t += __longlong_as_double(static_cast<long long>(w[u][0] | (static_cast<u64>(w[u][2]) << 32)));
         }
-    };
-    auto put_sum = [&](int slot, int v, double t) {
-        const u64 b = static_cast<u64>(__double_as_longlong(t));
-        __builtin_amdgcn_raw_buffer_store_b128(
-            u32x4{static_cast<uint32_t>(b), rt, static_cast<uint32_t>(b >> 32), rt}, sums, (slot * kSlotSums + v) * 16, 0, kAgent);
-    };
-    // sums of `count` slots, by the first wave, into s_tot (four lanes per value, a fixed order)
-    auto add_slots = [&](int count) {
-        static_assert(4 * NV <= 64, "four lanes per value");
-        if (tid < 64) {
-            const int v = tid >> 2, part = tid & 3;
-            double t = 0.0;
-            if (v < NV)
-                for (int s = part; s < count; s += 4) t += s_slot[s * NV + v];
-            t += __shfl_xor(t, 1, 64);
-            t += __shfl_xor(t, 2, 64);
-            if (part == 0 && v < NV) s_tot[v] = t;
-            // alpha and beta of the sets, lane 4 q for set q (meaningful after an iteration's sums only)
-            const double rr2 = __shfl(t, 4 * (2 * NS) + tid, 64), rzq = __shfl(t, 4 * (3 * NS) + tid, 64),
-                         qzq = __shfl(t, 4 * (4 * NS) + tid, 64);
-            if (part == 0 && v < NS) {
-                const double alpha = rr2 / t, est = rr2 - 2.0 * alpha * rzq + alpha * alpha * qzq;
-                s_al[v] = alpha;
-                s_be[v] = (est > 0.0 ? est : 0.0) / rr2;
-            }
-            // a snapshot that every thread reads after the next barrier: waits may run out at any time, but all
-            // threads leave together
-            if (tid == 0) s_end = s_bad;
-        }
+        t += __shfl_xor(t, 1, 64);
+        t += __shfl_xor(t, 2, 64);
+        return t;
     };
     // this workgroup's partial sums out (part: per thread); returns after they are stored
     auto send_sums = [&](const double (&part)[NV]) {
@@ -524,24 +531,18 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             put_sum((rt & 1) * kResMaxGroups + wg, tid, t);
         }
     };
-    // all workgroups' sums in: leaves the totals in s_slot's slots ready for add_slots(count), returns count
-    auto recv_sums = [&]() -> int {
-        const int own = (rt & 1) * kResMaxGroups;
-        if (G <= kFlatGroups) {
-            poll_slots(own, G);
-            return G;
-        }
-        const int grp = 2 * kResMaxGroups + (rt & 1) * kGroup, ng = (G + kGroup - 1) / kGroup;
-        if (wg % kGroup == 0) {
-            const int m = min(kGroup, G - wg);
-            poll_slots(own + wg, m);
-            lds_barrier();
-            add_slots(m);
-            lds_barrier();
-            if (tid < NV) put_sum(grp + wg / kGroup, tid, s_tot[tid]);
-        }
-        poll_slots(grp, ng);
-        return ng;
+    // A leader's sum of its group out, before anything else is waited for: every other workgroup waits for it.
+    auto lead = [&]() {
+        if (G <= kGroup || wg % kGroup != 0 || !summer) return;
+        const double t = wave_slots((rt & 1) * kResMaxGroups + wg, min(kGroup, G - wg));
+        if ((sl & 3) == 0 && (sl >> 2) < NV) put_sum(2 * kResMaxGroups + (rt & 1) * kGroup + wg / kGroup, sl >> 2, t);
+    };
+    // all workgroups' sums in: the totals for every thread; false when a wait of this round ran out
+    auto recv_sums = [&]() -> bool {
+        const int own = (rt & 1) * kResMaxGroups, grp = 2 * kResMaxGroups + (rt & 1) * kGroup;
+        if (summer) totals(G <= kGroup ? wave_slots(own, G) : wave_slots(grp, (G + kGroup - 1) / kGroup));
+        lds_barrier();
+        return (s_bad | s_end) == 0;
     };
 
     if constexpr (kLdsRows) {
@@ -608,7 +609,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                     for (int c = 0; c < NC; ++c) v[0][c] = c >= c0 && c < c0 + XC ? a.x[static_cast<size_t>(c) * n + g] : 0.0;
                 } else {
                     const int sl[1] = {ly.slot[g]};
-                    fetch(sl, v);
+                    fetch(sl, v, s_bad);
                 }
                 X hv;
 #pragma unroll
@@ -660,12 +661,9 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         ++rt;
         send_sums(part);
         T hq[kHB][NC];
-        fetch(hid, hq);
-        int count = recv_sums();
-        lds_barrier();
-        add_slots(count);
-        lds_barrier();
-        if (s_end) {
+        lead();
+        fetch(hid, hq, s_bad);
+        if (!recv_sums()) {
             status = RES_TIMEOUT;
             break;
         }
@@ -678,7 +676,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         for (int h = tid + kHB * kTh; h < nhalo; h += kTh) {
             T v[1][NC];
             const int sl[1] = {slot_of(h)};
-            fetch(sl, v);
+            fetch(sl, v, s_late);
 #pragma unroll
             for (int c = 0; c < NC; ++c) hr[h * NC + c] = v[0][c];
         }
@@ -774,8 +772,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 ended = k == budget;
             }
             // the first streamed entries are on their way while the vectors are updated
-            Entries<T, BLK, kLdsRows ? kAhead : 1> ahead;
-            if constexpr (kLdsRows) {
+            Entries<T, BLK, (kAhead > 0 ? kAhead : 1)> ahead;
+            if constexpr (kAhead > 0) {
                 const int row = base_row(), g = n0 + (row < cnt ? row : 0);
                 load_entries<T, BLK, L, kAhead, END_SELECT>(A, ly.col, slice_of(ly, g), g & 63, l, (E + a.lds_entries) * L, row, ahead);
                 __builtin_amdgcn_sched_barrier(0);
@@ -842,7 +840,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 for (int c = 0; c < NC; ++c) q[0][c] = T(0);
                 if (k > 0) {
                     const int sl[1] = {slot_of(h)};
-                    fetch(sl, q);
+                    fetch(sl, q, s_late);
                 }
                 halo(h, q[0]);
             }
@@ -889,7 +887,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                         one.c[0] = sc_col[u * a.lds_threads + tid];
                         add_entries<T, NC, BLK, L, 1, END_LOADED>(one, sc, l, 0, none, f, base, acc);
                     }
-                    add_entries<T, NC, BLK, L, kAhead, END_SELECT>(ahead, sc, l, (E + a.lds_entries) * L, none, f, base, acc);
+                    if constexpr (kAhead > 0)
+                        add_entries<T, NC, BLK, L, kAhead, END_SELECT>(ahead, sc, l, (E + a.lds_entries) * L, none, f, base, acc);
                 }
                 const int held = (E + (kLdsRows ? a.lds_entries + kAhead : 0)) * L;
                 if (sc.w > held) add_rest<T, NC, BLK, L>(A, ly.col, sc, g & 63, l, held, none, f, base, acc);
@@ -912,12 +911,9 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             }
             if constexpr (kBuf > 1) fill(base_row(), en[0]);
             send_sums(part);
-            fetch(hid, hq);
-            count = recv_sums();
-            lds_barrier();
-            add_slots(count);
-            lds_barrier();
-            if (s_end) {
+            lead();
+            fetch(hid, hq, s_bad);
+            if (!recv_sums()) {
                 status = RES_TIMEOUT;
                 break;
             }
@@ -1008,9 +1004,8 @@ const void *entry_of(int nc, bool blk, int nbr) {
 
 // dynamic LDS of a launch
 template <class T>
-size_t lds_bytes(const ResArgs &a, int nc, bool blk) {
-    const size_t nv = blk ? 5 : 5 * static_cast<size_t>(nc);
-    return sizeof(double) * kMaxSlots * nv + a.stage_bytes + sizeof(T) * ((nc + 1) * static_cast<size_t>(a.ly.nhalo_max) + 2) +
+size_t lds_bytes(const ResArgs &a, int nc) {
+    return a.stage_bytes + sizeof(T) * ((nc + 1) * static_cast<size_t>(a.ly.nhalo_max) + 2) +
            (6 * sizeof(T) + sizeof(uint16_t)) * static_cast<size_t>(a.lds_entries) * a.lds_threads;
 }
 
@@ -1031,7 +1026,7 @@ bool resident_fits(ResArgs &a, int nc, bool blk, size_t lds_max, int cus) {
     a.lds_threads = std::min(kTh, (ly.nbr * lanes + 63) / 64 * 64);
     // the kernel's static LDS besides
     constexpr size_t kStatic = 4096;
-    if (lds_bytes<T>(a, nc, blk) + kStatic > lds_max) return false;
+    if (lds_bytes<T>(a, nc) + kStatic > lds_max) return false;
     if (blk && sizeof(T) == 8 && rpt == 1 && lanes <= 2) {
         // At 97k nodes four of 14 FP64 blocks per row are in registers; streaming the other ten (48 MB an iteration,
         // 6 MB for each XCD's 4 MB of L2) took 14.6 us of a 21 us iteration.  What LDS has left holds five more, and
@@ -1039,10 +1034,10 @@ bool resident_fits(ResArgs &a, int nc, bool blk, size_t lds_max, int cus) {
         const int e = resident_entries(false, true, lanes, rpt);
         const size_t each = (6 * sizeof(T) + sizeof(uint16_t)) * static_cast<size_t>(a.lds_threads);
         const int most = std::max(0, (ly.wmax + lanes - 1) / lanes - e);
-        a.lds_entries = std::min<int>(most, static_cast<int>((lds_max - kStatic - lds_bytes<T>(a, nc, blk)) / each));
+        a.lds_entries = std::min<int>(most, static_cast<int>((lds_max - kStatic - lds_bytes<T>(a, nc)) / each));
     }
     int per_cu = 0;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kTh, lds_bytes<T>(a, nc, blk)) == hipSuccess &&
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kTh, lds_bytes<T>(a, nc)) == hipSuccess &&
            per_cu >= 1;
 }
 
@@ -1053,7 +1048,7 @@ int launch_resident(const ResArgs &a, int nc, bool blk, hipStream_t s) {
     ResArgs v = a;
     void *args[] = {&v};
     return static_cast<int>(
-        hipLaunchCooperativeKernel(k, dim3(a.ly.G), dim3(kTh), args, static_cast<unsigned>(lds_bytes<T>(a, nc, blk)), s));
+        hipLaunchCooperativeKernel(k, dim3(a.ly.G), dim3(kTh), args, static_cast<unsigned>(lds_bytes<T>(a, nc)), s));
 }
 
 }  // namespace gspm

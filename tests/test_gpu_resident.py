@@ -3,7 +3,7 @@ inside the kernel), at the sizes where their split changes.
 
 A mesh of N unique nodes is dealt out in blocks of 64 k rows to at most one
 workgroup per CU; 64 rows take eight lanes each, 256 take two, 512 one, and
-larger blocks two to eight rows per thread.  Up to 64 workgroups read each
+larger blocks two to eight rows per thread.  Up to 16 workgroups read each
 other's sums directly, more of them through leaders.  The sizes below lie on
 both sides of these edges, with ragged last blocks, a last block of a single
 row, inclusions (rows without entries), node orders whose halo lists are longer
@@ -26,8 +26,7 @@ pytestmark = pytest.mark.gpu
 
 TOL = 1e-9
 # axis nodes -> unique nodes: 5 -> 64 (one full block), 6 -> 125 (a block and 61 rows), 9 -> 512, 17 -> 4096 (64
-# blocks of 64: every sum read directly), 18 -> 4913 (39 blocks of 128), 25 -> 13824, 27 -> 17576 (blocks of 128, more
-# than 64 of them), 35 -> 39304, 48 -> 103823, 53 -> 140608 (two rows per thread)
+# blocks of 64, four leaders), 18 -> 4913, 25 -> 13824, 27 -> 17576 (blocks of 128), 35 -> 39304, 48 -> 103823, 53 -> 140608 (two rows per thread)
 CASES = [(5, "kuhn", 0.0, gspm.GSPM_REORDER_MORTON), (6, "kuhn", 0.0, gspm.GSPM_REORDER_MORTON),
          (9, "kuhn", 0.3, gspm.GSPM_REORDER_MORTON), (17, "kuhn", 0.0, gspm.GSPM_REORDER_MORTON),
          (18, "kuhn", 0.3, gspm.GSPM_REORDER_NONE), (19, "five", 0.25, gspm.GSPM_REORDER_MORTON),
@@ -109,4 +108,24 @@ def test_rotated_stiffness_rows_follow_set_params():
         x, it = sim.solve(gspm.GSPM_OP_ELASTIC, b, tol=TOL)
         r = b - sim.apply(gspm.GSPM_OP_ELASTIC, x)
         assert it > 0 and np.linalg.norm(r) <= 2.0 * TOL * np.linalg.norm(b)
+    sim.close()
+
+
+# axis nodes -> unique nodes: 11 -> 1000 (16 blocks of 64: one hop), 12 -> 1331 (11 of 128), 13 -> 1728, 14 -> 2197 (35 of
+# 64: a third leader with three), 26 -> 15625 (245), 33 -> 32768 (256 of 128), 34 -> 35937 (188 of 192: two lanes a row)
+@pytest.mark.parametrize("precision", [gspm.GSPM_FP64, gspm.GSPM_MIXED])
+@pytest.mark.parametrize("n", [11, 12, 13, 14, 26, 33, 34])
+def test_hops_and_lanes(n, precision):
+    case, sim = _setup(n, "kuhn", 0.0, gspm.GSPM_REORDER_MORTON, precision, precond=False)
+    rng = np.random.default_rng(n + 2)
+    b = _load(case, sim, gspm.GSPM_OP_ELASTIC, 0.0, rng)
+    x, _ = sim.solve(gspm.GSPM_OP_ELASTIC, b, tol=TOL)
+    sites = np.unique(case.mesh.per_site(np.arange(case.mesh.n_sites, dtype=float)[:, None] + np.zeros((1, 3)))[:, 0],
+                      return_index=True)[1]
+    r = (b - sim.apply(gspm.GSPM_OP_ELASTIC, x))[sites]
+    held = np.any(x[sites] != 0, axis=1)          # the pinned node has no equation
+    assert np.count_nonzero(~held) <= 1
+    assert np.linalg.norm(r[held]) <= 2 * TOL * np.linalg.norm(b[sites][held])
+    again, _ = sim.solve(gspm.GSPM_OP_ELASTIC, b, tol=TOL)
+    assert np.array_equal(again, x)
     sim.close()
