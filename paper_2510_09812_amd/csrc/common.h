@@ -242,12 +242,13 @@ struct GreenView {
     int32_t gx, gy, gz, gxh;      // grid points per axis; gxh = gx / 2 + 1 (half spectrum along x)
     int64_t G, Gh;                // grid points, half-spectrum modes (gz x gy x gxh)
     double lo[3], h[3];           // grid origin and spacing
-    const int32_t *rptr, *rnode;  // restriction lists: row t gathers (rnode, rw)[rptr[t] .. rptr[t + 1])
+    const int32_t *rptr, *rnode;  // restriction lists: row t gathers (rnode, rw)[rptr[t] .. rptr[t + 1]), a multiple of four
     const int32_t *rgrid;         // the grid point of row t (rows run in Morton order of the grid points)
     const void *rw;               // their weights (T)
     const void *dinv;             // [3][n] omega / diag(K^mech) (T)
     const void *ainv;             // A(k)^-1 / G, Hermitian: re a00 a11 a22, then a01 a02 a12 (re, im) (T); [Gh][9], or as
                                   // the own transforms read it (launch_pc_symbol)
+    void *r4;                     // [n][4] r of the last update, for the restriction (T)
     void *grid;                   // [2][G] complex (T): x0 + i x1, x2 on the grid (restriction in, prolongation out)
     void *spec;                   // [2][G] complex (T): their spectra (forward FFT out, inverse FFT in)
 };
@@ -255,7 +256,7 @@ struct GreenView {
 // The preconditioner's node and grid passes (green_kernels.hip).  Every
 // launch returns at once when the scalar set has converged.
 template <class T>
-void launch_pc_restrict(const GreenView &gv, int n, const T *r, const CGScalars &cg, int test_k, double tol,
+void launch_pc_restrict(const GreenView &gv, int n, const T *r, bool node4, const CGScalars &cg, int test_k, double tol,
                         hipStream_t s);
 template <class T>
 void launch_pc_modes(const GreenView &gv, const CGScalars &cg, hipStream_t s);
@@ -264,7 +265,8 @@ void launch_pc_prolong(const GreenView &gv, const MeshView &mv, const T *r, T *z
                        hipStream_t s);
 // x += alpha p, r -= alpha q with alpha = rz[k] / pq[k]; rr[k + 1] += r.r.
 template <class T>
-void launch_pcg_update(int n, T *x, T *r, const T *p, const T *q, const CGScalars &cg, int k, hipStream_t s);
+void launch_pcg_update(const GreenView &gv, int n, T *x, T *r, const T *p, const T *q, const CGScalars &cg, int k,
+                       hipStream_t s);
 // b -= mean(b) per component; bb (zeroed here) += b.b.  aux: 3 x kShards doubles.
 void launch_remove_mean3(int n, double *b, double *aux, double *bb, hipStream_t s, const DetSums &det = DetSums{});
 // x -= x(p0) on every node.  aux: 3 doubles.

@@ -143,7 +143,7 @@ struct GreenState {
     double sym_key[37] = {};      // the Voigt stiffness (36) and scale the symbol and diagonal were built for
     GreenView gv{};
     int32_t *rptr = nullptr, *rgrid = nullptr, *rnode = nullptr;
-    void *rw = nullptr, *dinv = nullptr, *ainv = nullptr, *grid = nullptr, *spec = nullptr, *work = nullptr;
+    void *rw = nullptr, *dinv = nullptr, *ainv = nullptr, *r4 = nullptr, *grid = nullptr, *spec = nullptr, *work = nullptr;
     double *aux = nullptr;        // 3 x kShards: mean sums; then 3: the pinned node's shift
     size_t work_bytes = 0;
     bool own_fft = false;         // the transforms of green_fft.hip (fft, tables); else rocFFT's
@@ -284,9 +284,9 @@ GsRowsView gs_rows(gspm_ctx *c, double eps, double mass, bool fp32);
 int green_apply64(gspm_ctx *c, const double *x, double *y);
 // z = B r on the context's stream, T the preconditioner's precision: tests |r|
 // as iteration test_k first (test_k < 0: no test) and does nothing once
-// converged; rz += r.z.
+// converged; rz += r.z.  updated: r is as launch_pcg_update left it.
 template <class T>
-int green_precond(gspm_ctx *c, const T *r, T *z, double *rz, const CGScalars &cg, int test_k, double tol);
+int green_precond(gspm_ctx *c, const T *r, bool updated, T *z, double *rz, const CGScalars &cg, int test_k, double tol);
 int hip_check(gspm_ctx *c, hipError_t e, const char *what);
 // Device memory of the context: the caller's allocator when given, else hipMalloc / hipFree.
 int ctx_malloc(gspm_ctx *c, void **p, size_t bytes, const char *what);

@@ -312,11 +312,12 @@ int setup_mesh_part(gspm_ctx *c) {
         rgrid[t] = order[t].second;
         row_of[static_cast<size_t>(order[t].second)] = static_cast<int32_t>(t);
     }
-    std::vector<int32_t> ptr(static_cast<size_t>(gv.G) + 1, 0), node(8 * static_cast<size_t>(n));
+    // a row's list is padded to a multiple of four entries, of weight zero, for 16-byte loads
+    std::vector<int32_t> ptr(static_cast<size_t>(gv.G) + 1, 0);
     for (int64_t q : gidx) ++ptr[static_cast<size_t>(row_of[static_cast<size_t>(q)]) + 1];
-    for (int64_t q = 0; q < gv.G; ++q) ptr[q + 1] += ptr[q];
-    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
-    std::vector<double> w64(8 * static_cast<size_t>(n));
+    for (int64_t q = 0; q < gv.G; ++q) ptr[q + 1] = ptr[q] + (ptr[q + 1] + 3) / 4 * 4;
+    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1), node(static_cast<size_t>(ptr.back()), 0);
+    std::vector<double> w64(node.size(), 0.0);
     for (int i = 0; i < n; ++i)      // nodes in order within each list
         for (int cc = 0; cc < 8; ++cc) {
             const size_t e = 8 * static_cast<size_t>(i) + cc;
@@ -324,12 +325,15 @@ int setup_mesh_part(gspm_ctx *c) {
             node[slot] = i;
             w64[slot] = wts[e];
         }
+    for (int64_t q = 0; q < gv.G; ++q)      // the padding gathers what the row gathers anyway
+        for (int32_t e = fill[q]; e < ptr[q + 1]; ++e) node[e] = node[ptr[q]];
     const size_t tb = f32 ? sizeof(float) : sizeof(double);
     rc = pc_alloc(c, &pc.rptr, ptr.size());
     if (!rc) rc = pc_alloc(c, &pc.rgrid, rgrid.size());
     if (!rc) rc = pc_alloc(c, &pc.rnode, node.size());
     if (!rc) rc = pc_alloc(c, reinterpret_cast<char **>(&pc.rw), tb * w64.size());
     if (!rc) rc = pc_alloc(c, reinterpret_cast<char **>(&pc.dinv), tb * 3 * static_cast<size_t>(n));
+    if (!rc) rc = pc_alloc(c, reinterpret_cast<char **>(&pc.r4), tb * 4 * static_cast<size_t>(n));
     if (!rc) rc = pc_alloc(c, reinterpret_cast<char **>(&pc.ainv), tb * 9 * static_cast<size_t>(gv.Gh));
     if (!rc) rc = pc_alloc(c, reinterpret_cast<char **>(&pc.grid), tb * 4 * static_cast<size_t>(gv.G));
     if (!rc) rc = pc_alloc(c, reinterpret_cast<char **>(&pc.spec), tb * 4 * static_cast<size_t>(gv.G));
@@ -352,6 +356,7 @@ int setup_mesh_part(gspm_ctx *c) {
     gv.rnode = pc.rnode;
     gv.rw = pc.rw;
     gv.dinv = pc.dinv;
+    gv.r4 = pc.r4;
     gv.ainv = pc.ainv;
     gv.grid = pc.grid;
     gv.spec = pc.spec;
@@ -447,10 +452,10 @@ int library_fft(gspm_ctx *c, bool forward) {
 }  // namespace
 
 template <class T>
-int green_precond(gspm_ctx *c, const T *r, T *z, double *rz, const CGScalars &cg, int test_k, double tol) {
+int green_precond(gspm_ctx *c, const T *r, bool updated, T *z, double *rz, const CGScalars &cg, int test_k, double tol) {
     auto &pc = c->pc;
     int rc = GSPM_OK;
-    launch_pc_restrict<T>(pc.gv, c->n, r, cg, test_k, tol, c->stream);
+    launch_pc_restrict<T>(pc.gv, c->n, r, updated, cg, test_k, tol, c->stream);
     if (pc.own_fft) {
         launch_pc_fft<T>(pc.gv, pc.fft, cg, c->stream);
     } else {
@@ -462,13 +467,13 @@ int green_precond(gspm_ctx *c, const T *r, T *z, double *rz, const CGScalars &cg
     return rc;
 }
 
-template int green_precond<double>(gspm_ctx *, const double *, double *, double *, const CGScalars &, int, double);
-template int green_precond<float>(gspm_ctx *, const float *, float *, double *, const CGScalars &, int, double);
+template int green_precond<double>(gspm_ctx *, const double *, bool, double *, double *, const CGScalars &, int, double);
+template int green_precond<float>(gspm_ctx *, const float *, bool, float *, double *, const CGScalars &, int, double);
 
 int green_apply64(gspm_ctx *c, const double *x, double *y) {
     // a fresh scalar set: the passes test nothing (test_k < 0) and run
     cg_prepare(c, 1);
-    const int rc = green_precond<double>(c, x, y, c->cg.rq_at(0), c->cg, -1, 0.0);
+    const int rc = green_precond<double>(c, x, false, y, c->cg.rq_at(0), c->cg, -1, 0.0);
     return rc ? rc : hip_check(c, hipStreamSynchronize(c->stream), "apply(PRECOND)");
 }
 
@@ -481,7 +486,7 @@ void gspm_ctx::release_pc() {
     if (q.inv) rocfft_plan_destroy(static_cast<rocfft_plan>(q.inv));
     if (q.info) rocfft_execution_info_destroy(static_cast<rocfft_execution_info>(q.info));
     for (void *p : {static_cast<void *>(q.rptr), static_cast<void *>(q.rgrid), static_cast<void *>(q.rnode), q.rw,
-                    q.dinv, q.ainv, q.grid, q.spec, q.work, q.tables, static_cast<void *>(q.aux)})
+                    q.dinv, q.ainv, q.r4, q.grid, q.spec, q.work, q.tables, static_cast<void *>(q.aux)})
         gspm::ctx_free(this, p);
     q = gspm::GreenState{};
 }

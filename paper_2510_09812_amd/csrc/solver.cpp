@@ -518,7 +518,7 @@ auto pcg_iteration(gspm_ctx *c, const MeshView &mvu, T *x, T *r, T *z, T *pa, T 
         if (last) return;                  // |r| of the last iteration was tested by its own preconditioner pass
         hipStream_t s = c->stream;
         auto precond = [&](int test_k) {
-            const int rc = green_precond<T>(c, r, z, pcg_rz_at(cg, test_k), cg, test_k, tol);
+            const int rc = green_precond<T>(c, r, test_k > 0, z, pcg_rz_at(cg, test_k), cg, test_k, tol);
             if (rc && !*fft_rc) *fft_rc = rc;
         };
         if (k == 0 || c->pc_owed) {
@@ -528,7 +528,7 @@ auto pcg_iteration(gspm_ctx *c, const MeshView &mvu, T *x, T *r, T *z, T *pa, T 
         T *pin = (k & 1) ? pa : pb, *pout = (k & 1) ? pb : pa;
         launch_elastic_pcg<T>(mvu, c->mat, k, z, pin, pout, q, cg, s, prof_begin(c, k));
         prof_end(c);
-        launch_pcg_update<T>(c->n, x, r, pout, q, cg, k, s);
+        launch_pcg_update<T>(c->pc.gv, c->n, x, r, pout, q, cg, k, s);
         if (k == c->batch_last) {
             launch_cg_check(3, true, cg, k + 1, tol, s);
             c->pc_owed = true;

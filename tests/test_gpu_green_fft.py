@@ -59,7 +59,8 @@ def test_preconditioner_over_grid_lengths(n, stretch):
 
 
 @pytest.mark.parametrize("n,stretch", [(5, (1, 1, 1)), (14, (1, 1, 1)), (25, (1, 1, 1)), (32, (1, 1, 1)),
-                                       (11, (1.8, 0.9, 0.7)), (62, (1, 1, 1))])
+                                       (11, (1.8, 0.9, 0.7)), (62, (1, 1, 1)),
+                                       (82, (1, 1, 1))])    # 531441 nodes: several a thread in the prolongation
 def test_fp32_transforms_precondition_as_fp64(n, stretch):
     case, p = _case(n, stretch)
     rng = np.random.default_rng(n + 1)
