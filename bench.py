@@ -508,8 +508,9 @@ def main() -> int:
         if pst["gs_matvec_ms"] > pst["matvec_ms"]:
             launches, tot_ms = pst["gs_matvec_launches"], pst["gs_matvec_ms"]
             mb = gs3_iteration_bytes(n, ne_mag, rb, jacobi=precond)
-            kname = f"k_gs_rows_cg<{tname},3>" + (" (Jacobi)" if precond else "")
-            what = "GS CG iteration launch on three components"
+            # in the mixed form the 1M-node solves run whole in one launch, timed over their iterations
+            kname = (f"k_resident<{tname},3>" if mixed else f"k_gs_rows_cg<{tname},3>") + (" (Jacobi)" if precond else "")
+            what = "GS CG iteration on three components"
             traffic = traffic_from_profile("gs", ("mixed" if mixed else "fp64") + ("+precond" if precond else ""),
                                            case.name)
         else:
