@@ -106,10 +106,11 @@ struct ResComm {
 struct OperatorRows {
     bool tried = false, ready = false;    // the pattern
     bool k_ready = false, m_ready = false;
+    bool looked = false, closed = false;  // K^mech: whether its blocks are symmetric (no free surface), else no rows
     ResLayout ly{};
     ResComm comm;
     int64_t nent = 0;
-    int32_t *inc_ptr = nullptr, *inc = nullptr, *tets = nullptr;
+    int32_t *inc_ptr = nullptr, *inc = nullptr, *tets = nullptr, *open = nullptr;
     double key[36] = {};                  // the stiffness of k64
     double *k64 = nullptr, *m64 = nullptr;
     float *k32 = nullptr, *m32 = nullptr;

@@ -5,11 +5,14 @@
 // bit), and adds the product of the two gradients of those that hold j:
 //   G_ab = sum_e V g_i,a g_j,b
 // from which K^ms_ij = G_aa and (K^mech_ij)_pq = C_apbq G_ab.  The stiffness is
-// one C on a periodic cell, so G (by parts: int d_a phi_i d_b phi_j equals int
-// d_b phi_i d_a phi_j) and with it every 3x3 block is symmetric and six numbers
-// hold it.  The diagonal is minus the sum of the row and not stored; the pinned
-// node's row is zero.  Run once per mesh (K^ms) or
-// stiffness (K^mech): about 0.3 ms at 97k nodes.
+// one C, so on a periodic cell that the elements fill G (by parts: int d_a phi_i
+// d_b phi_j equals int d_b phi_i d_a phi_j) and with it every 3x3 block is
+// symmetric and six numbers hold it.  Free surfaces (a cavity, a gap, a body
+// that does not reach its box) leave a boundary term in G: a first run looks for
+// one, and with it the element kernels keep the elastic solve.  The diagonal is
+// minus the sum of the row and not stored; the pinned node's row is zero.  Run
+// once per mesh (the look at G, K^ms) or stiffness (K^mech): about 0.3 ms at 97k
+// nodes each.
 #include "device_common.h"
 #include "resident.h"
 
@@ -18,6 +21,13 @@ namespace gspm {
 namespace {
 
 constexpr int kVoigt[3][3] = {{0, 5, 4}, {5, 1, 3}, {4, 3, 2}};
+
+// |G_ab - G_ba| over sum_e V |g_i| |g_j| up to which an edge counts as closed.
+// Rounding leaves 1e-16 on compact elements, growing with their aspect (1e-14
+// at 100); a surface of flat faces leaves a sixth of the length across the edge
+// where the sum is a length over the elements' aspect.  Sliver meshes beyond
+// this line are solved with the elements, the slower way and right as well.
+constexpr double kClosed = 1e-11;
 
 }  // namespace
 
@@ -44,7 +54,7 @@ __global__ void __launch_bounds__(kThreads) k_operator_rows(const OperatorBuild 
         }
         const int c = ly.col[beg + 64 * e + lane];
         const int j = c < ly.nbr ? g * ly.nbr + c : ly.halo_ids[hb + c - ly.nbr];
-        double G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        double G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, size = 0.0;
         // a padding entry's column is the row itself: zero
         const bool want = i != a.p0 && j != i;
         for (int t = a.inc_ptr[i]; want && t < a.inc_ptr[i + 1]; ++t) {
@@ -77,7 +87,12 @@ __global__ void __launch_bounds__(kThreads) k_operator_rows(const OperatorBuild 
             for (int p = 0; p < 3; ++p)
 #pragma unroll
                 for (int q = 0; q < 3; ++q) G[p][q] += geo.vol * gi[p] * gj[q];
+            size += geo.vol * sqrt((gi[0] * gi[0] + gi[1] * gi[1] + gi[2] * gi[2]) *
+                                   (gj[0] * gj[0] + gj[1] * gj[1] + gj[2] * gj[2]));
         }
+        if (a.open && !(fmax(fabs(G[0][1] - G[1][0]), fmax(fabs(G[0][2] - G[2][0]), fabs(G[1][2] - G[2][1]))) <=
+                        kClosed * size))
+            *a.open = 1;
         if (a.m64 || a.m32) {
             const double v = G[0][0] + G[1][1] + G[2][2];
             const size_t o = static_cast<size_t>(beg) + 64 * e + lane;

@@ -74,6 +74,7 @@ struct OperatorBuild {
     double scale_k, scale_m;           // of the FP32 copies
     double *k64, *m64;
     float *k32, *m32;
+    int32_t *open;                     // set to 1 when a free surface makes blocks of K^mech asymmetric
 };
 void launch_operator_rows(OperatorBuild a, hipStream_t s);
 

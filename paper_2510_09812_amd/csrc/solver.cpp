@@ -355,6 +355,7 @@ bool build_pattern(gspm_ctx *c) {
         m.take(o.inc_ptr, inc_ptr.size());
         m.take(o.inc, inc.size());
         m.take(o.tets, c->tets_int.size());
+        m.take(o.open, 1);
         if (shared) return;
         m.take(off, rows.off.size());
         m.take(col, rl.col.size());
@@ -404,6 +405,19 @@ bool operator_rows(gspm_ctx *c, bool elastic) {
     b.p0 = c->p0;
     std::memcpy(b.C6, c->mat.C6, sizeof b.C6);
     const double ls = c->mv.len_scale;
+    if (elastic && !o.looked) {
+        // once per mesh, before its memory is taken: are the blocks symmetric?
+        int32_t *open = reinterpret_cast<int32_t *>(c->h_step + 8);
+        *open = 1;
+        launch_fill_i32(o.open, 1, 0, c->stream);
+        b.open = o.open;
+        launch_operator_rows(b, c->stream);
+        launch_i32_to_host(o.open, 1, open, c->stream);
+        o.closed = hipStreamSynchronize(c->stream) == hipSuccess && *open == 0;
+        o.looked = true;
+        b.open = nullptr;
+    }
+    if (elastic && !o.closed) return false;
     if (elastic) {
         if (!o.k64 && !ops_alloc(c, [&](OpsMemory &m) {
                 m.take(o.k64, 6 * ne);
