@@ -919,10 +919,20 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             }
         }
         if (status == RES_TIMEOUT) break;
+        int most = 0;
 #pragma unroll
         for (int q = 0; q < NS; ++q)
-            if (!conv[q]) total[q] += iters[q];
+            if (!conv[q]) {
+                total[q] += iters[q];
+                most = max(most, iters[q]);
+            }
         if (kMixed && status == RES_NONFINITE) break;
+        // an inner solve without an iteration (the scaled residual is below FP32's range and its norm reads zero) leaves
+        // x as it was, and so would every one after it
+        if (kMixed && most == 0) {
+            status = RES_NOCONV;
+            break;
+        }
         if (kMixed) ++refinements;
         // x <- x + d (mixed) or the accumulated x; the next residual needs it from the neighbours
         ++xt;

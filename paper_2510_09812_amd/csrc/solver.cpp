@@ -191,6 +191,8 @@ CgResult cg_fp64(gspm_ctx *c, int nc, bool joint, double *x, double tol, int max
     return r;
 }
 
+constexpr const char *kBelowF32 = "the FP32 inner solve cannot reduce the residual: it is below the range of FP32";
+
 // Mixed form: FP64 iterative refinement around FP32 CG.  Each outer step
 // computes the true residual r = b - A x with the FP64 operator and stops
 // when ||r|| <= tol ||b|| for every component (the same criterion as the
@@ -275,8 +277,19 @@ CgResult cg_mixed(gspm_ctx *c, int nc, bool joint, double *x, double tol, int ma
             res.status = in.status;
             return res;
         }
+        int most = 0;
         for (int q = 0; q < ns; ++q)
-            if (!conv[q]) total[q] += in.iters[q];
+            if (!conv[q]) {
+                total[q] += in.iters[q];
+                most = std::max(most, in.iters[q]);
+            }
+        // an inner solve without an iteration (the scaled residual is below FP32's range and its norm reads zero)
+        // leaves x as it was, and so would every one after it
+        if (most == 0) {
+            res.status = GSPM_E_NOCONV;
+            c->err = kBelowF32;
+            break;
+        }
         launch_add_f32(static_cast<int64_t>(nc) * n, x, c->d.x32, s);
         ++c->refinements;
         if (kind == SK_MECH) ++c->mech_refinements;
@@ -501,7 +514,7 @@ bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, 
     if (kind == SK_MECH) c->mech_refinements += o.refinements;
     if (o.status == RES_NOCONV) {
         res.status = GSPM_E_NOCONV;
-        c->err = "CG did not converge within cg_maxit iterations";
+        c->err = most >= maxit ? "CG did not converge within cg_maxit iterations" : kBelowF32;
     } else if (o.status == RES_NONFINITE) {
         res.status = GSPM_E_NONFINITE;
         c->err = "non-finite CG residual";
