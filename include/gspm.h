@@ -248,6 +248,21 @@ typedef enum {
  * 11 doubles per node of device memory (allocated with the mesh). */
 gspm_status gspm_set_gs_start(gspm_ctx *ctx, int32_t mode);
 
+typedef enum {
+    GSPM_PATH_AUTO = 0,     /* a whole solve in one launch where the mesh allows it (the default) */
+    GSPM_PATH_LAUNCHES = 1, /* a launch (or a few) for each CG iteration */
+    GSPM_PATH_GAVE_UP = 2   /* get only: by launches, because a one-launch solve failed or waited too long */
+} gspm_solve_path;
+
+/* How the CG solves run.  In a one-launch solve the workgroups wait for each
+ * other; one that waits longer than max_wait seconds (0: 5 s; another process
+ * on the device can cause it) gives up, and the solve and the later ones on
+ * the mesh run by launches.  Results keep their accuracy, iterations cost up to
+ * four times as much.  set_solve_path(GSPM_PATH_AUTO) tries one launch again;
+ * get_solve_path tells which way the next solve goes. */
+gspm_status gspm_set_solve_path(gspm_ctx *ctx, int32_t path, double max_wait);
+gspm_status gspm_get_solve_path(gspm_ctx *ctx, int32_t *path);
+
 /* Set or read a nodal field (n_nodes x 3, caller's order; GSPM_FIELD_UD:
  * n_nodes values).  Setting M normalises m on magnetic nodes (a vector whose
  * length is 1 to within 1e-14 is kept as given, so a state read with

@@ -936,6 +936,24 @@ gspm_status gspm_get_field(gspm_ctx *c, gspm_field which, double *out, int64_t n
     return static_cast<gspm_status>(user_get(c, src, which == GSPM_FIELD_UD ? 1 : 3, out));
 }
 
+gspm_status gspm_set_solve_path(gspm_ctx *c, int32_t path, double max_wait) {
+    if (!c) return GSPM_E_ARG;
+    if (path != GSPM_PATH_AUTO && path != GSPM_PATH_LAUNCHES) return fail(c, GSPM_E_ARG, "set_solve_path: unknown path");
+    if (!(max_wait >= 0.0 && max_wait <= 3600.0)) return fail(c, GSPM_E_ARG, "set_solve_path: max_wait must be 0 to 3600 s");
+    hipSetDevice(c->device);
+    c->one_launch = path == GSPM_PATH_AUTO;
+    c->res_wait = max_wait > 0.0 ? static_cast<int64_t>(max_wait * 1e8) : kResWaitTicks;
+    if (c->one_launch && c->res_off) resident_restart(c);
+    return GSPM_OK;
+}
+
+gspm_status gspm_get_solve_path(gspm_ctx *c, int32_t *path) {
+    if (!c) return GSPM_E_ARG;
+    if (!path) return fail(c, GSPM_E_ARG, "get_solve_path: null pointer");
+    *path = !c->one_launch ? GSPM_PATH_LAUNCHES : c->res_off ? GSPM_PATH_GAVE_UP : GSPM_PATH_AUTO;
+    return GSPM_OK;
+}
+
 gspm_status gspm_step(gspm_ctx *c, double dt, int32_t n_steps, gspm_step_stats *stats) {
     if (!c) return GSPM_E_ARG;
     if (!c->have_mesh || !c->have_params || !c->have_m)

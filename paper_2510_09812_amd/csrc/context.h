@@ -245,6 +245,8 @@ struct gspm_ctx {
     bool all_magnetic = false;            // every element is magnetic: the GS rows' pattern is that of all elements
     gspm::ResResult *h_res = nullptr;     // pinned (after h_step's sums): the running solve's outcome
     bool res_off = false;                 // a launch failed or ran out of time: launch-per-iteration from then on
+    bool one_launch = true;               // gspm_set_solve_path
+    int64_t res_wait = gspm::kResWaitTicks;
     size_t lds_max = 0;
     int cus = 0;
 
@@ -270,6 +272,8 @@ CgResult cg_gs(gspm_ctx *c, int nc, double eps, double *x, const double *b, doub
 CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int maxit, SolveKind kind);
 // Clears the resident solves' exchange buffers and tags on the context's stream.
 void resident_reset(gspm_ctx *c, const ResLayout &ly, const ResComm &comm);
+// The same for every layout of the context, after a launch that gave up.
+void resident_restart(gspm_ctx *c);
 // The rows of K^mech (elastic) or K^ms for the resident solves, built when
 // missing or out of date; false when the mesh is too large for them or memory
 // is short (the matrix-free kernels serve then).

@@ -15,6 +15,8 @@ constexpr int kGroup = 16;             // workgroups that read each other's sums
 constexpr int kSlotSums = 16;          // sums per slot, 16 bytes each
 constexpr int kResChunks = 3;          // 16-byte chunks per exchanged node: three doubles
 constexpr double kResInnerFloor = 1e-6;
+constexpr int64_t kResWaitTicks = 500000000;   // 5 s
+constexpr int64_t kResWaitShort = 1000;        // waits below look at the clock at every poll
 
 enum ResStatus { RES_OK = 0, RES_NOCONV = 1, RES_NONFINITE = 2, RES_TIMEOUT = 3 };
 
@@ -37,9 +39,11 @@ struct ResLayoutHost {
     std::vector<int32_t> slot;
 };
 
-// What the host reads back (pinned host memory, written by the launch's end).
+// What the host reads back (pinned host memory, written by the launch's end):
+// workgroup 0's outcome, which every workgroup shares unless a wait ran out in
+// some of them, and whether one did in any (cleared by the host before).
 struct ResResult {
-    int32_t status, refinements, stale;
+    int32_t status, refinements, stale, gave_up;
     int32_t iters[kMaxComp];
     double relres[kMaxComp];
 };
@@ -55,6 +59,7 @@ struct ResArgs {
     double tol, tol2;
     int32_t maxit, jacobi;
     int32_t zero_sum;                  // the rows sum to zero (K^mech, K^ms): no diagonals given
+    int64_t wait_ticks;                // of the 100 MHz clock: the longest wait for another workgroup
     void *xq, *slots;
     uint32_t *epoch;                   // [2]: last tags of the exchange and of the sums
     ResResult *result;

@@ -39,10 +39,13 @@
 // All totals are added in a fixed order, the same in every workgroup, so all
 // take the same decisions, and results repeat bitwise.
 //
-// Every wait is bounded (kSpinTicks of the 100 MHz clock): a workgroup whose
-// wait runs out leaves with status RES_TIMEOUT and the host takes the
-// launch-per-iteration path.  Cooperative launches are resident as a whole, so
-// this does not happen short of a fault elsewhere.
+// Every wait is bounded (wait_ticks of the 100 MHz clock, 5 s unless the caller
+// says otherwise): a workgroup whose wait runs out says so to the host and
+// leaves, the others' waits run out in turn, and the host solves again from
+// what x holds with a launch per iteration.  Cooperative launches are resident
+// as a whole, but the clock runs on while the device serves another process,
+// so a wait can run out in one workgroup and not in another: the outcome
+// workgroup 0 reports counts only if none gave up.
 #pragma once
 
 #include <algorithm>
@@ -58,7 +61,6 @@ namespace {
 using u64 = unsigned long long;
 
 constexpr int kTh = kResThreads;
-constexpr long long kSpinTicks = 500000000;    // 5 s
 constexpr int kHB = 4;                         // halo nodes per thread polled while the sums are on their way
 
 // Nodes' values travel in 16-byte chunks of two words, each word with its own
@@ -94,15 +96,14 @@ struct Wire {
 };
 
 struct Spin {
-    long long t0;
+    long long t0 = 0;
     int n = 0;
-    __device__ __forceinline__ Spin() : t0(0) {}
-    // true when the wait has run out
-    __device__ __forceinline__ bool over() {
-        if ((++n & 255) != 0) return false;
+    // true when the wait has run out (the clock is looked at every 256 polls)
+    __device__ __forceinline__ bool over(long long ticks) {
+        if ((++n & 255) != 0 && ticks >= kResWaitShort) return false;
         const long long t = wall_clock64();
         if (t0 == 0) t0 = t;
-        return t - t0 > kSpinTicks;
+        return t - t0 > ticks;
     }
 };
 
@@ -445,7 +446,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
 #pragma unroll
                     for (int j = 0; j < W::kChunks; ++j) ok &= w[u][j][1] == xt && w[u][j][3] == xt;
             if (ok) break;
-            if (spin.over()) {
+            if (spin.over(a.wait_ticks)) {
                 bad = 1;
                 break;
             }
@@ -462,10 +463,12 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     // the workgroups' slots of NV sums, and the leaders'
     const __amdgpu_buffer_rsrc_t sums = __builtin_amdgcn_make_buffer_rsrc(
         a.slots, 0, static_cast<int>(resident_slot_bytes()), 0x00027000);
-    auto put_sum = [&](int slot, int v, double t) {
+    // (a sum that is not to be used goes out under the tag of the round before last, which nobody waits for)
+    auto put_sum = [&](int slot, int v, double t, bool good) {
         const u64 b = static_cast<u64>(__double_as_longlong(t));
+        const uint32_t tag = good ? rt : rt - 2;
         __builtin_amdgcn_raw_buffer_store_b128(
-            u32x4{static_cast<uint32_t>(b), rt, static_cast<uint32_t>(b >> 32), rt}, sums, (slot * kSlotSums + v) * 16, 0, kAgent);
+            u32x4{static_cast<uint32_t>(b), tag, static_cast<uint32_t>(b >> 32), tag}, sums, (slot * kSlotSums + v) * 16, 0, kAgent);
     };
     // The totals of value sl >> 2 (four lanes of one wave a value, in a fixed order) into s_tot,
     // and alpha and beta of the sets, by the lanes of sums 0 to NS - 1 (meaningful after an iteration's sums only).
@@ -486,12 +489,14 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         }
         if (sl == 0) s_end = s_late;
     };
-    // the sum of up to kGroup slots, by that wave alone and straight from the loads
-    auto wave_slots = [&](int first, int count) -> double {
+    // the sum of up to kGroup slots, by that wave alone and straight from the loads; over: this
+    // lane's wait ran out
+    auto wave_slots = [&](int first, int count, bool &over) -> double {
         static_assert(kGroup == 16, "four slots a lane");
         const int v = sl >> 2, part = sl & 3;
         u32x4 w[4];
         double t = 0.0;
+        over = false;
         if (v < NV) {
             Spin spin;
             for (;;) {
@@ -505,7 +510,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 for (int u = 0; u < 4; ++u)
                     if (part + 4 * u < count) ok &= w[u][1] == rt && w[u][3] == rt;
                 if (ok) break;
-                if (spin.over()) {
+                if (spin.over(a.wait_ticks)) {
+                    over = true;
                     s_bad = 1;
                     break;
                 }
@@ -520,27 +526,34 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         t += __shfl_xor(t, 2, 64);
         return t;
     };
-    // this workgroup's partial sums out (part: per thread); returns after they are stored
+    // this workgroup's partial sums out (part: per thread); returns after they are stored.  Those of
+    // a workgroup that gave up are not good: no workgroup completes a round, and so stores an x, that values which never
+    // came had a part in
     auto send_sums = [&](const double (&part)[NV]) {
         wave_sums<NV>(part, s_part[tid >> 6]);
         lds_barrier();
         if (tid < NV) {
+            const int gone = s_bad | s_late;       // read along with the sums
             double t = 0.0;
 #pragma unroll
             for (int w = 0; w < kTh / 64; ++w) t += s_part[w][tid];
-            put_sum((rt & 1) * kResMaxGroups + wg, tid, t);
+            put_sum((rt & 1) * kResMaxGroups + wg, tid, t, gone == 0);
         }
     };
     // A leader's sum of its group out, before anything else is waited for: every other workgroup waits for it.
     auto lead = [&]() {
         if (G <= kGroup || wg % kGroup != 0 || !summer) return;
-        const double t = wave_slots((rt & 1) * kResMaxGroups + wg, min(kGroup, G - wg));
-        if ((sl & 3) == 0 && (sl >> 2) < NV) put_sum(2 * kResMaxGroups + (rt & 1) * kGroup + wg / kGroup, sl >> 2, t);
+        bool over;
+        const double t = wave_slots((rt & 1) * kResMaxGroups + wg, min(kGroup, G - wg), over);
+        const bool good = !__any(over);
+        if ((sl & 3) == 0 && (sl >> 2) < NV)
+            put_sum(2 * kResMaxGroups + (rt & 1) * kGroup + wg / kGroup, sl >> 2, t, good);
     };
     // all workgroups' sums in: the totals for every thread; false when a wait of this round ran out
     auto recv_sums = [&]() -> bool {
         const int own = (rt & 1) * kResMaxGroups, grp = 2 * kResMaxGroups + (rt & 1) * kGroup;
-        if (summer) totals(G <= kGroup ? wave_slots(own, G) : wave_slots(grp, (G + kGroup - 1) / kGroup));
+        bool over;
+        if (summer) totals(G <= kGroup ? wave_slots(own, G, over) : wave_slots(grp, (G + kGroup - 1) / kGroup, over));
         lds_barrier();
         return (s_bad | s_end) == 0;
     };
@@ -961,6 +974,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         --xt;                                       // the loop's head steps to this tag
         lds_barrier();
     }
+    if (status == RES_TIMEOUT && tid == 0) a.result->gave_up = 1;
     if (wg == 0 && tid == 0) {
         a.epoch[0] = xt + 2;
         a.epoch[1] = rt + 1;

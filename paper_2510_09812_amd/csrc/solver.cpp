@@ -306,6 +306,12 @@ void resident_reset(gspm_ctx *c, const ResLayout &ly, const ResComm &m) {
     launch_fill_i32(reinterpret_cast<int32_t *>(m.epoch), 2, 1, c->stream);
 }
 
+void resident_restart(gspm_ctx *c) {
+    if (c->res_gs.nbr) resident_reset(c, c->res_gs, c->res_gs_comm);
+    if (c->ops.ready && c->ops.comm.xq != c->res_gs_comm.xq) resident_reset(c, c->ops.ly, c->ops.comm);
+    c->res_off = false;
+}
+
 namespace {
 
 // Rows per workgroup up to which K^mech runs in row form: 26 bytes of FP32
@@ -399,7 +405,7 @@ bool build_pattern(gspm_ctx *c) {
 
 bool operator_rows(gspm_ctx *c, bool elastic) {
     auto &o = c->ops;
-    if (c->res_off || resident_rows(c->n, c->cus) == 0) return false;
+    if (!c->one_launch || c->res_off || resident_rows(c->n, c->cus) == 0) return false;
     if (elastic && resident_rows(c->n, c->cus) > kResElasticRows) return false;
     if (!o.tried) {
         o.tried = true;
@@ -461,12 +467,13 @@ namespace {
 
 // A whole solve in one launch (resident_kernel.h): the operator's rows and their
 // layout in `a`, its coefficients in the working type and in FP64.  False when
-// the launch does not fit the device or did not run; nothing has been changed
-// then beyond refinements of x, and the launch-per-iteration path takes over.
+// the launch does not fit the device, did not run or gave up in any of its
+// workgroups; x has been refined at most then (rows of some workgroups and not
+// of others: a start like any other), and the launch-per-iteration path takes over.
 template <class T>
 bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, double *x, const double *b, double tol, int maxit,
                  SolveKind kind, CgResult &res) {
-    if (c->res_off || a.ly.nbr == 0) return false;
+    if (!c->one_launch || c->res_off || a.ly.nbr == 0) return false;
     if (!resident_fits<T>(a, nc, blk, c->lds_max, c->cus)) return false;
     a.x = x;
     a.b = b;
@@ -478,8 +485,10 @@ bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, 
     a.slots = comm.slots;
     a.epoch = comm.epoch;
     a.result = c->h_res;
+    a.wait_ticks = c->res_wait;
     hipStream_t s = c->stream;
     c->h_res->status = RES_TIMEOUT;
+    c->h_res->gave_up = 0;
     const hipEvent_t *ev = prof_begin(c, 0);
     if (ev) hipEventRecord(ev[0], s);
     const int e = launch_resident<T>(a, nc, blk, s);
@@ -493,11 +502,11 @@ bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, 
     res.status = hip_check(c, hipStreamSynchronize(s), "CG");
     if (res.status) return true;
     const ResResult &o = *c->h_res;
-    if (o.stale) resident_reset(c, a.ly, comm);
-    if (o.status == RES_TIMEOUT) {
-        c->res_off = true;
+    if (o.gave_up || o.status == RES_TIMEOUT) {
+        c->res_off = true;                 // the exchange's tags are out of step: resident_restart before the next
         return false;
     }
+    if (o.stale) resident_reset(c, a.ly, comm);
     const int ns = blk ? 1 : nc;
     int most = 0;
     double worst = 0.0;
