@@ -500,9 +500,15 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
     if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
         return fail(c, GSPM_E_DEVICE, "upload_mesh: cannot query the compute units");
     ResLayoutHost rl;
-    const int32_t res_nbr = resident_rows(hm.n, c->cus);
+    const int32_t res_nbr = resident_rows(hm.n, c->cus, c->precision == GSPM_MIXED);
     bool resident = res_nbr > 0;
     if (resident) resident = resident_layout(rows, hm.n, res_nbr, rl);
+    if (resident) {
+        // (two components need less LDS than three, and serve a step's second stage by themselves)
+        ResLayout ly{};
+        ly.n = hm.n; ly.nbr = rl.nbr; ly.G = rl.G; ly.nhalo_max = rl.nhalo_max; ly.nexp = rl.nexp; ly.wmax = rl.wmax;
+        resident = resident_serves(c, ly, 2, false);
+    }
     // deterministic mode: per owned node its element copies, (copy index within the block's list) << 2 | slot
     std::vector<int32_t> inc_ptr;
     std::vector<uint16_t> inc_ent;

@@ -105,6 +105,7 @@ struct ResComm {
 // K^ms once.
 struct OperatorRows {
     bool tried = false, ready = false;    // the pattern
+    bool judged = false, k_fits = false, m_fits = false;   // whether solves on its layout fit the device
     bool k_ready = false, m_ready = false;
     bool looked = false, closed = false;  // K^mech: whether its blocks are symmetric (no free surface), else no rows
     ResLayout ly{};
@@ -270,6 +271,8 @@ CgResult cg_elastic(gspm_ctx *c, double *x, const double *b, double tol, int max
 CgResult cg_gs(gspm_ctx *c, int nc, double eps, double *x, const double *b, double tol, int maxit, SolveKind kind);
 // K^ms x = b (Eq. weak_demag) on nc components, pinned node p0.
 CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int maxit, SolveKind kind);
+// Whether a solve of nc components (or 3x3 blocks) on the layout fits the device.
+bool resident_serves(gspm_ctx *c, const ResLayout &ly, int nc, bool blk);
 // Clears the resident solves' exchange buffers and tags on the context's stream.
 void resident_reset(gspm_ctx *c, const ResLayout &ly, const ResComm &comm);
 // The same for every layout of the context, after a launch that gave up.

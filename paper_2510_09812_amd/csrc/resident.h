@@ -95,8 +95,9 @@ bool operator_pattern(int32_t n, const std::vector<int32_t> &tets, const std::ve
 // The columns of `rows` (any row blocks) for workgroups of nbr rows; false
 // when a workgroup would stage more than 65535 nodes.
 bool resident_layout(const GsRowsHost &rows, int32_t n, int32_t nbr, ResLayoutHost &out);
-// Rows per workgroup (a multiple of 64) for n nodes on a device of `cus` compute units (0: the mesh is too large).
-int32_t resident_rows(int32_t n, int32_t cus);
+// Rows per workgroup (a multiple of 64) for n nodes on a device of `cus` compute units with iterations in FP32 or FP64
+// (0: the mesh is too large).
+int32_t resident_rows(int32_t n, int32_t cus, bool f32);
 // Components of x a residual stages at once.
 __host__ __device__ constexpr int resident_xc(bool f32, int nc, bool blk, int rpt) {
     return f32 && nc == 3 && !blk && rpt == 8 ? 2 : nc;

@@ -33,13 +33,13 @@ void for_each_part(int32_t n, Body body) {
 // 4.9 us with 64 rows, eight lanes each, and 7.4 with 192, two each).  kGroup of
 // them need one hop, and small meshes stop there as long as that leaves a
 // workgroup 128 rows, four lanes each (1728 nodes: 4.2 us against 4.5).
-int32_t resident_rows(int32_t n, int32_t cus) {
+int32_t resident_rows(int32_t n, int32_t cus, bool f32) {
     const int32_t most = std::min(cus, kResMaxGroups);
     if (most <= 0) return 0;
     const int32_t need = (n + most - 1) / most;
     int32_t nbr = std::max(64, (need + 63) / 64 * 64);
     if (n <= kGroup * 128) nbr = std::max(nbr, (((n + kGroup - 1) / kGroup) + 63) / 64 * 64);
-    return nbr <= 4096 ? nbr : 0;
+    return nbr <= (f32 ? 4096 : 2048) ? nbr : 0;      // eight rows a thread; FP64 has registers for four
 }
 
 bool node_elements(int32_t n, const std::vector<int32_t> &tets, std::vector<int32_t> &inc_ptr, std::vector<int32_t> &inc) {

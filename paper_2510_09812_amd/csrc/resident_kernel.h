@@ -1011,9 +1011,11 @@ const void *entry_for(int lanes, int rpt) {
         return lanes == 1 ? entry<T, NC, BLK, 1, 1>() : lanes == 2 ? entry<T, NC, BLK, 2, 1>()
              : lanes == 4 ? entry<T, NC, BLK, 4, 1>() : entry<T, NC, BLK, 8, 1>();
     if (rpt == 2) return entry<T, NC, BLK, 1, 2>();
-    if (rpt == 4) return entry<T, NC, BLK, 1, 4>();
-    if constexpr (sizeof(T) == 4)      // FP64 stops at four rows per thread: its registers
-        if (rpt == 8) return entry<T, NC, BLK, 1, 8>();
+    if constexpr (!BLK) {              // (blocks of coefficients stop at two rows per thread: kResElasticRows)
+        if (rpt == 4) return entry<T, NC, BLK, 1, 4>();
+        if constexpr (sizeof(T) == 4)  // FP64 stops at four: its registers
+            if (rpt == 8) return entry<T, NC, BLK, 1, 8>();
+    }
     return nullptr;
 }
 

@@ -3,7 +3,9 @@
 //
 // CG runs without a host round trip per iteration.  Where the mesh allows it a
 // whole solve is one launch (cg_resident): the GS solves up to 4096 rows per
-// CU, the magnetostatic ones on the same terms, the elastic one up to 1024.
+// CU in the mixed form and 2048 in FP64, as far as the staging fits LDS, the
+// magnetostatic ones on the same terms, the elastic one up to 1024 on cells
+// without free surfaces.
 // Beyond, the elastic solve, the GS solves and the step's magnetostatic solve
 // run single-reduction CG by launches: one fused launch per iteration, which
 // completes the previous iteration (its scalars summed in the prologue), forms
@@ -306,6 +308,13 @@ void resident_reset(gspm_ctx *c, const ResLayout &ly, const ResComm &m) {
     launch_fill_i32(reinterpret_cast<int32_t *>(m.epoch), 2, 1, c->stream);
 }
 
+bool resident_serves(gspm_ctx *c, const ResLayout &ly, int nc, bool blk) {
+    ResArgs a{};
+    a.ly = ly;
+    return c->precision == GSPM_MIXED ? resident_fits<float>(a, nc, blk, c->lds_max, c->cus)
+                                      : resident_fits<double>(a, nc, blk, c->lds_max, c->cus);
+}
+
 void resident_restart(gspm_ctx *c) {
     if (c->res_gs.nbr) resident_reset(c, c->res_gs, c->res_gs_comm);
     if (c->ops.ready && c->ops.comm.xq != c->res_gs_comm.xq) resident_reset(c, c->ops.ly, c->ops.comm);
@@ -320,6 +329,8 @@ namespace {
 // (184 MB in FP64), which Infinity Cache still holds; at 1M nodes it would be
 // read from HBM in the time the matrix-free kernel takes (82 us).
 constexpr int kResElasticRows = 1024;
+
+int32_t rows_per_group(const gspm_ctx *c) { return resident_rows(c->n, c->cus, c->precision == GSPM_MIXED); }
 
 // Device memory of the operator rows, several buffers from one allocation:
 // take() in a first pass adds up sizes, in a second hands out the slices.
@@ -355,9 +366,11 @@ bool ops_upload(gspm_ctx *c, T *p, const std::vector<T> &h) {
     return h.empty() || hipMemcpyAsync(p, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice, c->stream) == hipSuccess;
 }
 
-bool build_pattern(gspm_ctx *c) {
+// The pattern on the host, whether solves on it fit the device and, if the one
+// asked for does, the device's copy.
+bool build_pattern(gspm_ctx *c, bool elastic) {
     auto &o = c->ops;
-    const int32_t nbr = resident_rows(c->n, c->cus);
+    const int32_t nbr = rows_per_group(c);
     if (nbr == 0 || c->tets_int.empty()) return false;
     std::vector<int32_t> inc_ptr, inc;
     if (!node_elements(c->n, c->tets_int, inc_ptr, inc)) return false;
@@ -368,6 +381,15 @@ bool build_pattern(gspm_ctx *c) {
     if (!shared && !(operator_pattern(c->n, c->tets_int, inc_ptr, inc, nbr, rows) &&
                      resident_layout(rows, c->n, nbr, rl)))
         return false;
+    ResLayout ly = c->res_gs;
+    if (!shared) {
+        ly = ResLayout{};
+        ly.n = c->n; ly.nbr = rl.nbr; ly.G = rl.G; ly.nhalo_max = rl.nhalo_max; ly.nexp = rl.nexp; ly.wmax = rl.wmax;
+    }
+    o.k_fits = nbr <= kResElasticRows && resident_serves(c, ly, 3, true);
+    o.m_fits = resident_serves(c, ly, 1, false);
+    o.judged = true;
+    if (!(elastic ? o.k_fits : o.m_fits)) return false;
     int32_t *off = nullptr, *halo_ptr = nullptr, *halo_ids = nullptr, *slot = nullptr;
     uint16_t *col = nullptr;
     bool ok = ops_alloc(c, [&](OpsMemory &m) {
@@ -393,7 +415,8 @@ bool build_pattern(gspm_ctx *c) {
     } else if (ok) {
         ok = ops_upload(c, off, rows.off) && ops_upload(c, col, rl.col) && ops_upload(c, halo_ptr, rl.halo_ptr) &&
              ops_upload(c, halo_ids, rl.halo_ids) && ops_upload(c, slot, rl.slot);
-        o.ly = ResLayout{off, col, halo_ptr, halo_ids, slot, c->n, rl.nbr, rl.G, rl.nhalo_max, rl.nexp, rl.wmax};
+        ly.off = off; ly.col = col; ly.halo_ptr = halo_ptr; ly.halo_ids = halo_ids; ly.slot = slot;
+        o.ly = ly;
         o.nent = static_cast<int64_t>(rl.col.size());
         resident_reset(c, o.ly, o.comm);
     }
@@ -405,11 +428,13 @@ bool build_pattern(gspm_ctx *c) {
 
 bool operator_rows(gspm_ctx *c, bool elastic) {
     auto &o = c->ops;
-    if (!c->one_launch || c->res_off || resident_rows(c->n, c->cus) == 0) return false;
-    if (elastic && resident_rows(c->n, c->cus) > kResElasticRows) return false;
+    if (!c->one_launch || c->res_off || rows_per_group(c) == 0) return false;
+    if (elastic && rows_per_group(c) > kResElasticRows) return false;
+    if (o.judged && !(elastic ? o.k_fits : o.m_fits)) return false;
     if (!o.tried) {
+        o.ready = build_pattern(c, elastic);
+        if (!o.ready && o.judged && !(elastic ? o.k_fits : o.m_fits)) return false;   // the other operator may fit
         o.tried = true;
-        o.ready = build_pattern(c);
     }
     if (!o.ready) return false;
     const bool mixed = c->precision == GSPM_MIXED;

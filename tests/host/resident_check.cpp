@@ -110,7 +110,7 @@ int main(int argc, char **argv) {
         printf("%s\n", err.c_str());
         return 1;
     }
-    const int n = M.n, nbr = resident_rows(n, atoi(argv[2]));
+    const int n = M.n, nbr = resident_rows(n, atoi(argv[2]), true);
     if (nbr <= 0 || nbr % 64) {
         printf("no rows per workgroup\n");
         return 1;
