@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -502,7 +503,13 @@ gspm_status gspm_upload_mesh(gspm_ctx *c, int64_t n_nodes, const double *xyz, in
     ResLayoutHost rl;
     const int32_t res_nbr = resident_rows(hm.n, c->cus, c->precision == GSPM_MIXED);
     bool resident = res_nbr > 0;
-    if (resident) resident = resident_layout(rows, hm.n, res_nbr, rl);
+    if (resident) {
+        try {
+            resident = resident_layout(rows, hm.n, res_nbr, rl);
+        } catch (const std::bad_alloc &) {
+            resident = false;
+        }
+    }
     if (resident) {
         // (two components need less LDS than three, and serve a step's second stage by themselves)
         ResLayout ly{};

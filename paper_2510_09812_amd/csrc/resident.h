@@ -83,6 +83,8 @@ struct OperatorBuild {
 };
 void launch_operator_rows(OperatorBuild a, hipStream_t s);
 
+// The host functions below throw std::bad_alloc when memory is short; callers
+// at the C interface go on without the one-launch form then.
 // The elements of each node, ascending; false when there are too many to index.
 bool node_elements(int32_t n, const std::vector<int32_t> &tets, std::vector<int32_t> &inc_ptr, std::vector<int32_t> &inc);
 // The pattern of those operators: each node's neighbours through its elements

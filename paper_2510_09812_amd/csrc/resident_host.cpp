@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <new>
 #include <thread>
 
 #include "resident.h"
@@ -11,19 +12,31 @@ namespace gspm {
 
 namespace {
 
-// body(k) for every k in [0, n) on the host's threads.
+// body(k) for every k in [0, n) on the host's threads, as many of them as there
+// are to have.  What a body throws (memory) ends the others and is thrown here as
+// std::bad_alloc once all have stopped.
 template <class Body>
 void for_each_part(int32_t n, Body body) {
     std::atomic<int32_t> next{0};
-    auto worker = [&]() {
-        for (int32_t k; (k = next.fetch_add(1)) < n;) body(k);
+    std::atomic<bool> failed{false};
+    auto worker = [&]() noexcept {
+        try {
+            for (int32_t k; !failed && (k = next.fetch_add(1)) < n;) body(k);
+        } catch (...) {
+            failed = true;
+        }
     };
     // (a thread costs about as much as 16 parts of the smallest meshes)
     const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     std::vector<std::thread> pool;
-    for (unsigned t = 1; t < hw && 16 * static_cast<int32_t>(t) < n; ++t) pool.emplace_back(worker);
+    try {
+        for (unsigned t = 1; t < hw && 16 * static_cast<int32_t>(t) < n; ++t) pool.emplace_back(worker);
+    } catch (...) {
+        // no more threads: those there are do the work
+    }
     worker();
     for (auto &t : pool) t.join();
+    if (failed) throw std::bad_alloc();
 }
 
 }  // namespace

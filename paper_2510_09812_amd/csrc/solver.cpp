@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 
 #include "context.h"
 
@@ -350,6 +351,7 @@ bool ops_alloc(gspm_ctx *c, Layout layout) {
     layout(m);
     void *v = nullptr;
     const std::string err = c->err;
+    c->ops.owned.reserve(c->ops.owned.size() + 1);
     if (ctx_malloc(c, &v, m.used, "operator rows")) {
         (void)hipGetLastError();
         c->err = err;                     // not a failure of the call: the matrix-free kernels serve
@@ -424,9 +426,7 @@ bool build_pattern(gspm_ctx *c, bool elastic) {
     return hipStreamSynchronize(c->stream) == hipSuccess && ok;
 }
 
-}  // namespace
-
-bool operator_rows(gspm_ctx *c, bool elastic) {
+bool build_rows(gspm_ctx *c, bool elastic) {
     auto &o = c->ops;
     if (!c->one_launch || c->res_off || rows_per_group(c) == 0) return false;
     if (elastic && rows_per_group(c) > kResElasticRows) return false;
@@ -486,6 +486,17 @@ bool operator_rows(gspm_ctx *c, bool elastic) {
     }
     launch_operator_rows(b, c->stream);
     return true;
+}
+
+}  // namespace
+
+bool operator_rows(gspm_ctx *c, bool elastic) {
+    try {
+        return build_rows(c, elastic);
+    } catch (const std::bad_alloc &) {
+        c->ops.tried = true;               // no host memory for the pattern: as without device memory
+        return false;
+    }
 }
 
 namespace {

@@ -81,3 +81,17 @@ def test_layouts_match_brute_force_under_sanitizers(checker, name):
     print(r.stdout.strip())
     assert r.returncode == 0, r.stdout + r.stderr[-3000:]
     assert "Sanitizer" not in r.stderr and "runtime error" not in r.stderr, r.stderr[-3000:]
+
+
+def test_memory_and_threads_that_run_out(tmp_path):
+    """A failing allocation on any thread reaches the caller as std::bad_alloc, a thread that cannot be had is done without."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / "resident_faults")
+    subprocess.check_call([hipcc, "-O1", "-g", "-std=c++17", "-pthread", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + CSRC, os.path.join(ROOT, "tests", "host", "resident_faults.cpp"),
+                           os.path.join(CSRC, "resident_host.cpp"), "-ldl", "-o", exe], stderr=subprocess.DEVNULL)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(r.stdout.strip())
+    assert r.returncode == 0, r.stdout + r.stderr[-2000:]
