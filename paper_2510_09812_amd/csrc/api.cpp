@@ -350,7 +350,7 @@ void gspm_ctx::release_ops() {
 void gspm_ctx::release_nn() {
     if (stream) hipStreamSynchronize(stream);
     auto &q = nn;
-    dev_free(this, q.gptr); dev_free(this, q.gnbr); dev_free(this, q.gedge); dev_free(this, q.master); dev_free(this, q.wr); dev_free(this, q.m1); dev_free(this, q.m2);
+    dev_free(this, q.gptr); dev_free(this, q.gedge); dev_free(this, q.master); dev_free(this, q.wr); dev_free(this, q.m1); dev_free(this, q.m2);
     dev_free(this, q.grad); dev_free(this, q.mats); dev_free(this, q.acts); dev_free(this, q.y); dev_free(this, q.red); dev_free(this, q.dvec);
     dev_free(this, q.du); dev_free(this, q.mp_in); dev_free(this, q.m_in);
     dev_free(this, q.gh); dev_free(this, q.gha); dev_free(this, q.gab); dev_free(this, q.gy); dev_free(this, q.part);

@@ -121,7 +121,7 @@ struct OperatorRows {
 // Device state of the learned warm start (allocated on first use).
 struct MpnnState {
     bool ready = false, have_params = false;
-    int32_t *gptr = nullptr, *gnbr = nullptr;
+    int32_t *gptr = nullptr;
     float *gedge = nullptr;
     int64_t nedges = 0;
     float *master = nullptr, *wr = nullptr, *m1 = nullptr, *m2 = nullptr, *grad = nullptr;

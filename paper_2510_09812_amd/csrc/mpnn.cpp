@@ -70,7 +70,6 @@ int nn_setup(gspm_ctx *c) {
     int rc = 0;
     rc = rc ? rc : nn_alloc(c, &nn.gptr, ptr.size());
     rc = rc ? rc : nn_alloc(c, &nn.gedge, 4 * nbr.size());
-    rc = rc ? rc : nn_alloc(c, &nn.gnbr, nbr.size());
     rc = rc ? rc : nn_alloc(c, &nn.master, kNParam);
     rc = rc ? rc : nn_alloc(c, &nn.wr, kNParam);
     rc = rc ? rc : nn_alloc(c, &nn.m1, kNParam);
@@ -90,19 +89,22 @@ int nn_setup(gspm_ctx *c) {
     rc = rc ? rc : nn_alloc(c, &nn.gy, 3 * n);
     nn.part_wgs = static_cast<int>(std::min<size_t>(256, std::max<size_t>(1, (n + 127) / 128)));
     rc = rc ? rc : nn_alloc(c, &nn.part, static_cast<size_t>(nn.part_wgs) * kPartStride);
+    int32_t *gnbr = nullptr;              // until the edges are formed
+    rc = rc ? rc : nn_alloc(c, &gnbr, nbr.size());
     if (rc) {
         c->release_nn();
         return rc;
     }
     hipStream_t s = c->stream;
     hipMemcpyAsync(nn.gptr, ptr.data(), sizeof(int32_t) * ptr.size(), hipMemcpyHostToDevice, s);
-    hipMemcpyAsync(nn.gnbr, nbr.data(), sizeof(int32_t) * std::max<size_t>(nbr.size(), 1), hipMemcpyHostToDevice, s);
+    if (!nbr.empty()) hipMemcpyAsync(gnbr, nbr.data(), sizeof(int32_t) * nbr.size(), hipMemcpyHostToDevice, s);
     nn.nedges = static_cast<int64_t>(nbr.size());
     // mean spacing: the edge of a cube split into 6 tetrahedra of the mean volume
     const double hbar = std::cbrt(6.0 * c->vc / static_cast<double>(c->ne));
     nn.graph = Graph{nn.gptr, nn.gedge, c->n, static_cast<float>(1.0 / hbar)};
-    mpnn::launch_edges(nn.graph, c->mv, nn.gnbr, nn.gedge, s);
+    mpnn::launch_edges(nn.graph, c->mv, gnbr, nn.gedge, s);
     rc = hip_check(c, hipStreamSynchronize(s), "network setup");
+    ctx_free(c, gnbr);
     if (rc) {
         c->release_nn();
         return rc;
