@@ -283,12 +283,12 @@ int setup_mesh_part(gspm_ctx *c) {
                                                    ((cc & 4) ? t[2] : 1.0 - t[2]);
         }
     }
-    // the transforms: the library's only where planes or columns do not fit LDS (above about 140 points per axis in
-    // FP32, 100 in FP64).  Where they fit the own ones are the faster: an application's transforms and modes take
-    // 34 us against 165 at 46^3 (FP32) and 79 against 87 at 99^3
+    // the transforms: the own ones where their planes, columns and sums fit the chip and they are the faster, else the
+    // library's.  LDS holds planes of up to 143^2 points in FP32 and 101^2 in FP64; the registers of a stage end the
+    // own ones earlier for lengths of far-apart factors (94 = 2 x 47, 106 = 2 x 53, 143 = 11 x 13 and most from 129 on)
     int n1[3], n2[3];
     for (int a = 0; a < 3; ++a) split(g[a], n1[a], n2[a]);
-    pc.fft.wg_pairs = green_fft_fits(gv, n1, n2, f32, c->lds_max);
+    pc.fft.wg_pairs = green_fft_pairs(gv, n1, n2, f32, c->lds_max);
     pc.own_fft = pc.fft.wg_pairs > 0;
     // rows of the restriction run over the grid points in Morton order (the
     // nodes are Morton-numbered, so consecutive rows gather nearby nodes)

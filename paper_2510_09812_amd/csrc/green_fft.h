@@ -24,9 +24,10 @@ struct FftPlan {
     int32_t npairs, wg_pairs;          // wg_pairs: pairs of a workgroup of the z pass
 };
 
-// The pairs of a workgroup of the z pass; 0 when planes or columns do not fit
-// LDS (or a stage's outputs a wave's registers).
-int green_fft_fits(const GreenView &gv, const int n1[3], const int n2[3], bool f32, size_t lds_max);
+// The pairs of a workgroup of the z pass; 0 when the library's transforms serve:
+// planes or columns do not fit LDS or a stage's outputs a wave's registers, or
+// the library is the faster.
+int green_fft_pairs(const GreenView &gv, const int n1[3], const int n2[3], bool f32, size_t lds_max);
 // gv.grid (two packed complex fields) replaced by A_g^+ of itself over G;
 // returns at once when the scalar set has converged.
 template <class T>

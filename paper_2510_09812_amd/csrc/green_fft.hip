@@ -27,6 +27,8 @@
 // of 9 and 11 terms (N = 99) or 2 and 23 (N = 46) take more arithmetic than
 // butterflies for each radix would and need none for the factors a mesh
 // happens to have.
+#include <algorithm>
+
 #include "device_common.h"
 #include "green_fft.h"
 
@@ -286,22 +288,72 @@ int column_pairs(const GreenView &gv, int npairs, size_t cx, size_t lds_max) {
     return npairs >= 16 * 256 && column_lds(gv, 16, cx) <= lds_max ? 16 : 8;
 }
 
+// items of a stage: 64 sums of length r for kS pairs of outputs
+int stage_items(int r, int sums) { return ((sums + 63) / 64) * (fft_columns(r) / kS); }
+
 // whether a wave's registers hold its share of every stage's outputs
 bool items_fit(int n1, int n2, int lines, int threads, bool f32) {
     const int most = (f32 ? fft_items<float>() : fft_items<double>()) * (threads / 64);
-    auto items = [](int r, int sums) { return ((sums + 63) / 64) * (fft_columns(r) / kS); };
-    return (n1 == 1 || items(n1, n2 * lines) <= most) && items(n2, n1 * lines) <= most;
+    return (n1 == 1 || stage_items(n1, n2 * lines) <= most) && stage_items(n2, n1 * lines) <= most;
+}
+
+// The chain of a workgroup's transforms of `lines` lines: a wave's items times their terms, a quarter of a microsecond
+// each way for every unit.
+int chain(int n1, int n2, int lines, int threads) {
+    auto stage = [&](int r, int sums) {
+        const int waves = threads / 64;
+        return r == 1 ? 0 : (stage_items(r, sums) + waves - 1) / waves * (r / 2 + 1);
+    };
+    return stage(n1, n2 * lines) + stage(n2, n1 * lines);
+}
+
+// Whether the three launches beat the library's.  The sums' work grows with the lengths' factors and falls on few
+// workgroups where planes (films) or columns (rods) are few; the library's launches cost the same for all lengths of
+// small factors and several more for an axis with a prime above 13.  Iterations of the preconditioned solve (own
+// against library, us, FP32), over 150 grids:
+//   powers of 2, 3 or 5 throughout, where the library is at its best: 32^3 60 against 51, 27^3 57 / 51, 8 x 8 x 256 93 / 59,
+//     128 x 128 x 4 129 / 93;
+//   other small factors: the own ones up to a chain of 36 (30^3, 22: 60 / 63; 39^3, 30: 69 / 74; 64 x 64 x 24, 34: 83 / 87)
+//     or of 16 per 10^5 grid points, whose passes over memory cost the library more (120^3, 184: 425 / 481; 90^3, 115: 219
+//     / 240; 99^3, 131: 275 / 269), the library's beyond (72^3, 73: 150 / 139; 100 x 100 x 24, 62: 130 / 114);
+//   n axes with a larger prime: the own ones up to 100 n, more on large grids, which the library's extra launches cross
+//     each time (46^3, 50: 83 / 160; 97^3, 594: 322 / 443; 101 x 101 x 24, 323: 167 / 170; 24 x 24 x 127, 208: 116 / 93;
+//     127 x 127 x 24, 401: 254 / 218; 257 x 8 x 8, 400: 142 / 105).
+bool faster_than_library(const GreenView &gv, const int n1[3], const int n2[3], int pairs) {
+    const int g[3] = {gv.gx, gv.gy, gv.gz};
+    int pure = 0, large = 0;
+    for (int n : g) {
+        int rest = n, kinds = 0;
+        bool high = false;
+        for (int f = 2; rest > 1; ++f) {
+            if (rest % f) continue;
+            ++kinds;
+            high |= f > 5;
+            while (rest % f == 0) rest /= f;
+            large += f > 13 && rest == 1;
+        }
+        pure += kinds == 1 && !high;
+    }
+    if (pure == 3) return false;
+    constexpr int kCus = 256;
+    const int wgs = (gv.gxh * gv.gy + pairs - 1) / pairs;
+    const int64_t planes = (2 * gv.gz + kCus - 1) / kCus, columns = (wgs + kCus - 1) / kCus;
+    const int64_t work = planes * (chain(n1[0], n2[0], gv.gy, kPlaneThreads) + chain(n1[1], n2[1], gv.gx, kPlaneThreads)) +
+                         columns * chain(n1[2], n2[2], 4 * pairs, kColThreads);
+    const double points = static_cast<double>(gv.G);
+    return large == 0 ? work <= std::max(36.0, 1.6e-4 * points) : work <= 100.0 * large * (1.0 + points / 4e5);
 }
 
 }  // namespace
 
-int green_fft_fits(const GreenView &gv, const int n1[3], const int n2[3], bool f32, size_t lds_max) {
+int green_fft_pairs(const GreenView &gv, const int n1[3], const int n2[3], bool f32, size_t lds_max) {
     const size_t cx = f32 ? sizeof(Cx<float>) : sizeof(Cx<double>);
     if (plane_lds(gv, cx) > lds_max || !items_fit(n1[0], n2[0], gv.gy, kPlaneThreads, f32) ||
         !items_fit(n1[1], n2[1], gv.gx, kPlaneThreads, f32))
         return 0;
     for (int pairs = column_pairs(gv, gv.gxh * gv.gy, cx, lds_max); pairs >= 8; pairs /= 2)
-        if (column_lds(gv, pairs, cx) <= lds_max && items_fit(n1[2], n2[2], 4 * pairs, kColThreads, f32)) return pairs;
+        if (column_lds(gv, pairs, cx) <= lds_max && items_fit(n1[2], n2[2], 4 * pairs, kColThreads, f32))
+            return faster_than_library(gv, n1, n2, pairs) ? pairs : 0;
     return 0;
 }
 

@@ -1,5 +1,10 @@
-"""The elastic preconditioner on grids whose planes do not fit LDS, which the
-library transforms (and k_pc_modes with the symbol by mode) still serve.
+"""The elastic preconditioner on grids that the library transforms (with
+k_pc_modes and the symbol by mode): planes that do not fit LDS, powers of 2, 3
+or 5, and films and rods whose few planes or columns leave the own transforms
+on few workgroups; and grids next to those that take the own transforms.
+
+Films, rods and cubes on both sides of the choice: B x against the oracle's
+plain DFTs at the 1e-12 of the preconditioner's other tests.
 
 FP64, B x against the oracle on a 204 x 102 x 2 grid of cells of aspect 108:
 the symbol of a mode along the long edges is that much stiffer across them, so
@@ -63,6 +68,33 @@ def _slab(a, b, c):
     xyz[inner] += np.random.default_rng(5).uniform(-0.1 * H, 0.1 * H, (int(inner.sum()), 3))
     wrapped = ijk % (d - 1)
     return xyz, tets, (wrapped[:, 0] * b + wrapped[:, 1]) * c + wrapped[:, 2], np.array([a, b, c]) * H
+
+
+# pure powers (library), a rod of small factors at either side of the choice, rods and films with a prime at either side
+GRIDS = [(8, 8, 64), (9, 9, 9), (64, 4, 4), (12, 12, 50), (6, 6, 100), (4, 4, 61), (5, 5, 127), (61, 46, 3), (101, 67, 3),
+         (22, 22, 22)]
+
+
+@pytest.mark.parametrize("grid", GRIDS)
+def test_films_rods_and_cubes_against_the_oracle(grid):
+    xyz, tets, site, hi = _slab(*grid)
+    mesh = w.Mesh(xyz=xyz, tets=tets, tags=np.ones(len(tets), np.uint8), lo=np.zeros(3), hi=hi, n_axis=0, site=site)
+    p = dict(w.MATERIAL_FEGA, elastic_precond=gspm.GSPM_PRECOND_GREEN)
+    orc = O.Oracle.from_mesh(mesh)
+    orc.set_params(p)
+    assert tuple(orc.precond_grid()) == grid
+    sim = gspm.Simulation(mesh, p)
+    x = np.random.default_rng(3).standard_normal((int(np.prod(grid)), 3))[site]
+    xu = np.zeros((orc.n, 3))
+    nmap = orc.node_map()
+    xu[nmap] = x
+    y = sim.apply(gspm.GSPM_OP_PRECOND, x)
+    ref = orc.precond_apply(xu)[nmap]
+    err = np.abs(y - ref).max() / np.abs(ref).max()
+    print(f"{grid}: max rel err {err:.2e}", flush=True)
+    assert err < 1e-12
+    assert np.array_equal(sim.apply(gspm.GSPM_OP_PRECOND, x), y)
+    sim.close()
 
 
 def test_fp32_preconditions_as_fp64():
