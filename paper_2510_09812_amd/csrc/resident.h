@@ -16,7 +16,7 @@ constexpr int kSlotSums = 16;          // sums per slot, 16 bytes each
 constexpr int kResChunks = 3;          // 16-byte chunks per exchanged node: three doubles
 constexpr double kResInnerFloor = 1e-6;
 constexpr int64_t kResWaitTicks = 500000000;   // 5 s
-constexpr int64_t kResWaitShort = 1000;        // waits below look at the clock at every poll
+constexpr int64_t kResWaitShort = 1000;        // waits below look at the clock at every poll, others at every 256th
 
 enum ResStatus { RES_OK = 0, RES_NOCONV = 1, RES_NONFINITE = 2, RES_TIMEOUT = 3 };
 
@@ -60,6 +60,7 @@ struct ResArgs {
     int32_t maxit, jacobi;
     int32_t zero_sum;                  // the rows sum to zero (K^mech, K^ms): no diagonals given
     int64_t wait_ticks;                // of the 100 MHz clock: the longest wait for another workgroup
+    int32_t poll_mask;                 // polls between two looks at it, less one
     void *xq, *slots;
     uint32_t *epoch;                   // [2]: last tags of the exchange and of the sums
     ResResult *result;

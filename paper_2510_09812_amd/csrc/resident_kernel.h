@@ -98,12 +98,12 @@ struct Wire {
 struct Spin {
     long long t0 = 0;
     int n = 0;
-    // true when the wait has run out (the clock is looked at every 256 polls)
-    __device__ __forceinline__ bool over(long long ticks) {
-        if ((++n & 255) != 0 && ticks >= kResWaitShort) return false;
+    // true when the wait has run out (the clock is looked at every poll_mask + 1 polls)
+    __device__ __forceinline__ bool over(const ResArgs &a) {
+        if ((++n & a.poll_mask) != 0) return false;
         const long long t = wall_clock64();
         if (t0 == 0) t0 = t;
-        return t - t0 > ticks;
+        return t - t0 > a.wait_ticks;
     }
 };
 
@@ -339,8 +339,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     __shared__ double s_tot[NV];
     __shared__ double s_al[NS], s_be[NS], s_bb[NS];
     // a wait ran out: before the round's last barrier (stable from there to the next exchange), or in the halo beyond
-    // kHB nodes a thread, after it (seen a round later)
-    __shared__ int s_bad, s_late, s_end;
+    // kHB nodes a thread, after it (looked at behind the next barrier)
+    __shared__ int s_bad, s_late;
     const ResLayout &ly = a.ly;
     const int tid = threadIdx.x, n = ly.n, G = ly.G;
     const int wg = xcd_block(blockIdx.x, G);
@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     T *sk = hd + ((nhalo + 1) & ~1);               // [entry][6][lane] coefficients, then [entry][lane] columns
     uint16_t *sc_col = reinterpret_cast<uint16_t *>(sk + 6 * static_cast<size_t>(a.lds_entries) * a.lds_threads);
     const T *A = static_cast<const T *>(a.a), *D = static_cast<const T *>(a.d);
-    if (tid == 0) s_bad = s_late = s_end = 0;
+    if (tid == 0) s_bad = s_late = 0;
     uint32_t xt = a.epoch[0], rt = a.epoch[1];
 
     // export slots of the first halo nodes of this thread and of its rows, 1 / D of rows and halo
@@ -446,7 +446,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
 #pragma unroll
                     for (int j = 0; j < W::kChunks; ++j) ok &= w[u][j][1] == xt && w[u][j][3] == xt;
             if (ok) break;
-            if (spin.over(a.wait_ticks)) {
+            if (spin.over(a)) {
                 bad = 1;
                 break;
             }
@@ -463,10 +463,8 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
     // the workgroups' slots of NV sums, and the leaders'
     const __amdgpu_buffer_rsrc_t sums = __builtin_amdgcn_make_buffer_rsrc(
         a.slots, 0, static_cast<int>(resident_slot_bytes()), 0x00027000);
-    // (a sum that is not to be used goes out under the tag of the round before last, which nobody waits for)
-    auto put_sum = [&](int slot, int v, double t, bool good) {
+    auto put_sum = [&](int slot, int v, double t, uint32_t tag) {
         const u64 b = static_cast<u64>(__double_as_longlong(t));
-        const uint32_t tag = good ? rt : rt - 2;
         __builtin_amdgcn_raw_buffer_store_b128(
             u32x4{static_cast<uint32_t>(b), tag, static_cast<uint32_t>(b >> 32), tag}, sums, (slot * kSlotSums + v) * 16, 0, kAgent);
     };
@@ -487,7 +485,6 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             s_al[v] = alpha;
             s_be[v] = (est > 0.0 ? est : 0.0) / rr2;
         }
-        if (sl == 0) s_end = s_late;
     };
     // the sum of up to kGroup slots, by that wave alone and straight from the loads; over: this
     // lane's wait ran out
@@ -510,7 +507,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
                 for (int u = 0; u < 4; ++u)
                     if (part + 4 * u < count) ok &= w[u][1] == rt && w[u][3] == rt;
                 if (ok) break;
-                if (spin.over(a.wait_ticks)) {
+                if (spin.over(a)) {
                     over = true;
                     s_bad = 1;
                     break;
@@ -526,28 +523,26 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         t += __shfl_xor(t, 2, 64);
         return t;
     };
-    // this workgroup's partial sums out (part: per thread); returns after they are stored.  Those of
-    // a workgroup that gave up are not good: no workgroup completes a round, and so stores an x, that values which never
-    // came had a part in
+    // this workgroup's partial sums out (part: per thread); returns after they are stored
     auto send_sums = [&](const double (&part)[NV]) {
         wave_sums<NV>(part, s_part[tid >> 6]);
         lds_barrier();
         if (tid < NV) {
-            const int gone = s_bad | s_late;       // read along with the sums
             double t = 0.0;
 #pragma unroll
             for (int w = 0; w < kTh / 64; ++w) t += s_part[w][tid];
-            put_sum((rt & 1) * kResMaxGroups + wg, tid, t, gone == 0);
+            put_sum((rt & 1) * kResMaxGroups + wg, tid, t, rt);
         }
     };
-    // A leader's sum of its group out, before anything else is waited for: every other workgroup waits for it.
+    // A leader's sum of its group out, before anything else is waited for: every other workgroup waits for it.  One that
+    // is not whole, as a wait ran out, goes out under the tag of the round before last, which nobody waits for.
     auto lead = [&]() {
         if (G <= kGroup || wg % kGroup != 0 || !summer) return;
         bool over;
         const double t = wave_slots((rt & 1) * kResMaxGroups + wg, min(kGroup, G - wg), over);
         const bool good = !__any(over);
         if ((sl & 3) == 0 && (sl >> 2) < NV)
-            put_sum(2 * kResMaxGroups + (rt & 1) * kGroup + wg / kGroup, sl >> 2, t, good);
+            put_sum(2 * kResMaxGroups + (rt & 1) * kGroup + wg / kGroup, sl >> 2, t, good ? rt : rt - 2);
     };
     // all workgroups' sums in: the totals for every thread; false when a wait of this round ran out
     auto recv_sums = [&]() -> bool {
@@ -555,7 +550,7 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
         bool over;
         if (summer) totals(G <= kGroup ? wave_slots(own, G, over) : wave_slots(grp, (G + kGroup - 1) / kGroup, over));
         lds_barrier();
-        return (s_bad | s_end) == 0;
+        return s_bad == 0;
     };
 
     if constexpr (kLdsRows) {
@@ -672,6 +667,12 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             if (c0 + XC < NC) lds_barrier();       // the next components take the staging
         }
         ++rt;
+        // a workgroup that gave up keeps its sums back here and in the iterations: no round is completed, and so no x
+        // stored, that values which never came had a part in
+        if (outer > 0 && s_bad != 0) {
+            status = RES_TIMEOUT;
+            break;
+        }
         send_sums(part);
         T hq[kHB][NC];
         lead();
@@ -859,6 +860,10 @@ __global__ void __launch_bounds__(kTh) k_resident(const ResArgs a) {
             }
             if (k == 0 && tid == 0) f[zero] = V{};
             lds_barrier();
+            if (nhalo > kHB * kTh && s_late != 0) {
+                status = RES_TIMEOUT;
+                break;
+            }
             // q_k = A p_k and its sums
             ++xt;
             ++rt;

@@ -522,6 +522,7 @@ bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, 
     a.epoch = comm.epoch;
     a.result = c->h_res;
     a.wait_ticks = c->res_wait;
+    a.poll_mask = c->res_wait < kResWaitShort ? 0 : 255;
     hipStream_t s = c->stream;
     c->h_res->status = RES_TIMEOUT;
     c->h_res->gave_up = 0;
