@@ -290,13 +290,15 @@ void launch_elastic_pcg(const MeshView &mv, const Material &mat, int k, const T 
 void launch_fill(double *p, int64_t n, double v, hipStream_t s);
 
 // The caller's node order on the device: v is a staging copy of the caller's
-// node-major array (n0 x 3 or n0 x 1), err the least key of a failed check.
+// node-major array (n0 x 3 or n0 x 1), on the device or in pinned memory, dev a
+// device array for it (v itself or what v is copied to), err the least key of a
+// failed check.
 struct UserMap {
     int64_t n0;
     int32_t n, p0;
     const int32_t *user2int, *rep;
     const double *w;
-    double *v;
+    double *v, *dev;
     unsigned long long *err, *report;   // device; pinned host
 };
 // What put does with some nodes: nothing; normalise M and clear it off the

@@ -706,37 +706,69 @@ __device__ __forceinline__ double length3(const double (&x)[NC]) {
     return sqrt(x[0] * x[0] + x[NC > 1] * x[NC > 1] + x[NC > 2 ? 2 : 0] * x[NC > 2 ? 2 : 0]);
 }
 
-// Checks the caller's node-major array v (n0 x NC): every value finite, the
-// periodic copies of a node equal to its first to 1e-12, and, for M, no zero
-// vector on a magnetic node.  The least of the keys of what fails goes to *err
-// (UserKey), so that the report does not depend on the order of the threads.
+// The least key (UserKey) of what fails at node i of the caller's node-major
+// array v (n0 x NC): every value finite, the periodic copies of a node equal to
+// its first to 1e-12, and, for M, no zero vector on a magnetic node.  An array
+// staged in host memory is copied to dev on the way.
+template <int NC>
+__device__ __forceinline__ unsigned long long user_key(int64_t i, const int32_t *user2int, const int32_t *rep,
+                                                       const double *w, const double *v, double *dev, int kind,
+                                                       uint64_t key0) {
+    const int32_t k = user2int[i], f = rep[k];
+    unsigned long long least = kUserFine;
+    double x[NC];
+#pragma unroll
+    for (int a = 0; a < NC; ++a) {
+        x[a] = v[i * NC + a];
+        if (dev != v) dev[i * NC + a] = x[a];
+        const unsigned long long key = key0 | static_cast<uint64_t>((i * 3 + a) * 2);
+        if (!__builtin_isfinite(x[a])) {
+            least = min(least, key);
+        } else if (f != i) {
+            const double d = v[static_cast<int64_t>(f) * NC + a];
+            if (fabs(d - x[a]) > 1e-12 * fmax(fabs(d), fabs(x[a])))
+                least = min(least, key | static_cast<unsigned long long>(kUserMismatch));
+        }
+    }
+    if (NC == 3 && kind == USER_M && f == i && w[k] > 0.0 && !(length3(x) > 0.0))
+        least = min(least, static_cast<unsigned long long>(key0 | kUserZero));
+    return least;
+}
+
+// Node k of the checked array in internal order, component-major.
+template <int NC>
+__device__ __forceinline__ void user_write(int k, int n, int p0, const int32_t *rep, const double *w, const double *v,
+                                           int kind, double *dst) {
+    double x[NC];
+#pragma unroll
+    for (int a = 0; a < NC; ++a) x[a] = v[static_cast<int64_t>(rep[k]) * NC + a];
+    const bool zero = kind == USER_M || kind == USER_MAGNETIC ? !(w[k] > 0.0) : kind == USER_PINNED && k == p0;
+    if (NC == 3 && kind == USER_M && !zero) {
+        const double r = length3(x);
+        // a vector of unit length to rounding (a state read back) is kept bit for bit, so a saved state
+        // restores exactly
+        if (fabs(r - 1.0) > 1e-14) {
+#pragma unroll
+            for (int a = 0; a < NC; ++a) x[a] /= r;
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < NC; ++a) dst[static_cast<size_t>(a) * n + k] = zero ? 0.0 : x[a];
+}
+
+// The least of the keys goes to *err, so that the report does not depend on the order of the threads.
 template <int NC>
 __global__ void __launch_bounds__(kThreads) k_user_check(int64_t n0, const int32_t *user2int, const int32_t *rep,
-                                                         const double *w, const double *v, int kind, uint64_t key0,
-                                                         unsigned long long *err) {
+                                                         const double *w, const double *v, double *dev, int kind,
+                                                         uint64_t key0, unsigned long long *err) {
     for (int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; i < n0;
          i += static_cast<int64_t>(gridDim.x) * kThreads) {
-        const int32_t k = user2int[i], f = rep[k];
-        double x[NC];
-#pragma unroll
-        for (int a = 0; a < NC; ++a) {
-            x[a] = v[i * NC + a];
-            const uint64_t key = key0 | static_cast<uint64_t>((i * 3 + a) * 2);
-            if (!__builtin_isfinite(x[a])) {
-                atomicMin(err, static_cast<unsigned long long>(key));
-            } else if (f != i) {
-                const double d = v[static_cast<int64_t>(f) * NC + a];
-                if (fabs(d - x[a]) > 1e-12 * fmax(fabs(d), fabs(x[a])))
-                    atomicMin(err, static_cast<unsigned long long>(key | kUserMismatch));
-            }
-        }
-        if (NC == 3 && kind == USER_M && f == i && w[k] > 0.0 && !(length3(x) > 0.0))
-            atomicMin(err, static_cast<unsigned long long>(key0 | kUserZero));
+        const unsigned long long key = user_key<NC>(i, user2int, rep, w, v, dev, kind, key0);
+        if (key != kUserFine) atomicMin(err, key);
     }
 }
 
-// The checked array in internal order, component-major; nothing is written
-// once a check has failed.  `report` (pinned) receives *err.
+// Nothing is written once a check has failed.  `report` (pinned) receives *err.
 template <int NC>
 __global__ void __launch_bounds__(kThreads) k_user_put(int n, int p0, const int32_t *rep, const double *w,
                                                        const double *v, int kind, const unsigned long long *err,
@@ -744,23 +776,27 @@ __global__ void __launch_bounds__(kThreads) k_user_put(int n, int p0, const int3
     const unsigned long long e = *err;
     if (blockIdx.x == 0 && threadIdx.x == 0) *report = e;
     if (e != kUserFine) return;
-    for (int k = blockIdx.x * kThreads + threadIdx.x; k < n; k += gridDim.x * kThreads) {
-        double x[NC];
-#pragma unroll
-        for (int a = 0; a < NC; ++a) x[a] = v[static_cast<int64_t>(rep[k]) * NC + a];
-        const bool zero = kind == USER_M || kind == USER_MAGNETIC ? !(w[k] > 0.0) : kind == USER_PINNED && k == p0;
-        if (NC == 3 && kind == USER_M && !zero) {
-            const double r = length3(x);
-            // a vector of unit length to rounding (a state read back) is kept bit for bit, so a saved state
-            // restores exactly
-            if (fabs(r - 1.0) > 1e-14) {
-#pragma unroll
-                for (int a = 0; a < NC; ++a) x[a] /= r;
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < NC; ++a) dst[static_cast<size_t>(a) * n + k] = zero ? 0.0 : x[a];
+    for (int k = blockIdx.x * kThreads + threadIdx.x; k < n; k += gridDim.x * kThreads)
+        user_write<NC>(k, n, p0, rep, w, v, kind, dst);
+}
+
+// Both in one workgroup, for meshes whose array takes it no longer than a second launch takes (1000 nodes 21 -> 17 us a
+// call; 3375 nodes 25 -> 27).
+constexpr int kSmallThreads = 1024, kSmallNodes = 2048;
+template <int NC>
+__global__ void __launch_bounds__(kSmallThreads) k_user_put_small(UserMap u, int kind, uint64_t key0, double *dst) {
+    __shared__ unsigned long long least;
+    if (threadIdx.x == 0) least = *u.err;
+    __syncthreads();
+    for (int i = threadIdx.x; i < static_cast<int>(u.n0); i += kSmallThreads) {
+        const unsigned long long key = user_key<NC>(i, u.user2int, u.rep, u.w, u.v, u.dev, kind, key0);
+        if (key != kUserFine) atomicMin(&least, key);
     }
+    __syncthreads();
+    const unsigned long long e = least;
+    if (threadIdx.x == 0) *u.err = *u.report = e;
+    if (e != kUserFine) return;
+    for (int k = threadIdx.x; k < u.n; k += kSmallThreads) user_write<NC>(k, u.n, u.p0, u.rep, u.w, u.dev, kind, dst);
 }
 
 template <int NC>
@@ -777,12 +813,19 @@ __global__ void __launch_bounds__(kThreads) k_user_get(int64_t n0, int n, const 
 void launch_user_put(const UserMap &u, int nc, int kind, int seq, double *dst, hipStream_t s) {
     const uint64_t key0 = static_cast<uint64_t>(seq) << kUserSeqShift;
     const dim3 gc(node_grid(u.n0)), gp(node_grid(u.n)), t(kThreads);
+    if (u.n0 <= kSmallNodes) {
+        if (nc == 3)
+            hipLaunchKernelGGL(k_user_put_small<3>, dim3(1), dim3(kSmallThreads), 0, s, u, kind, key0, dst);
+        else
+            hipLaunchKernelGGL(k_user_put_small<1>, dim3(1), dim3(kSmallThreads), 0, s, u, kind, key0, dst);
+        return;
+    }
     if (nc == 3) {
-        hipLaunchKernelGGL(k_user_check<3>, gc, t, 0, s, u.n0, u.user2int, u.rep, u.w, u.v, kind, key0, u.err);
-        hipLaunchKernelGGL(k_user_put<3>, gp, t, 0, s, u.n, u.p0, u.rep, u.w, u.v, kind, u.err, dst, u.report);
+        hipLaunchKernelGGL(k_user_check<3>, gc, t, 0, s, u.n0, u.user2int, u.rep, u.w, u.v, u.dev, kind, key0, u.err);
+        hipLaunchKernelGGL(k_user_put<3>, gp, t, 0, s, u.n, u.p0, u.rep, u.w, u.dev, kind, u.err, dst, u.report);
     } else {
-        hipLaunchKernelGGL(k_user_check<1>, gc, t, 0, s, u.n0, u.user2int, u.rep, u.w, u.v, kind, key0, u.err);
-        hipLaunchKernelGGL(k_user_put<1>, gp, t, 0, s, u.n, u.p0, u.rep, u.w, u.v, kind, u.err, dst, u.report);
+        hipLaunchKernelGGL(k_user_check<1>, gc, t, 0, s, u.n0, u.user2int, u.rep, u.w, u.v, u.dev, kind, key0, u.err);
+        hipLaunchKernelGGL(k_user_put<1>, gp, t, 0, s, u.n, u.p0, u.rep, u.w, u.dev, kind, u.err, dst, u.report);
     }
 }
 
