@@ -242,7 +242,7 @@ struct GreenView {
     int32_t gx, gy, gz, gxh;      // grid points per axis; gxh = gx / 2 + 1 (half spectrum along x)
     int64_t G, Gh;                // grid points, half-spectrum modes (gz x gy x gxh)
     double lo[3], h[3];           // grid origin and spacing
-    const int32_t *rptr, *rnode;  // restriction lists: row t gathers (rnode, rw)[rptr[t] .. rptr[t + 1]), a multiple of four
+    const int32_t *rptr, *rnode;  // restriction lists: row t gathers (rnode, rw)[4 rptr[t] .. 4 rptr[t + 1])
     const int32_t *rgrid;         // the grid point of row t (rows run in Morton order of the grid points)
     const void *rw;               // their weights (T)
     const void *dinv;             // [3][n] omega / diag(K^mech) (T)

@@ -312,21 +312,24 @@ int setup_mesh_part(gspm_ctx *c) {
         rgrid[t] = order[t].second;
         row_of[static_cast<size_t>(order[t].second)] = static_cast<int32_t>(t);
     }
-    // a row's list is padded to a multiple of four entries, of weight zero, for 16-byte loads
+    // a row's list is padded to a multiple of four entries, of weight zero, for 16-byte loads; ptr counts fours, so that
+    // the padding does not lower the largest mesh that 32 bits index
     std::vector<int32_t> ptr(static_cast<size_t>(gv.G) + 1, 0);
     for (int64_t q : gidx) ++ptr[static_cast<size_t>(row_of[static_cast<size_t>(q)]) + 1];
-    for (int64_t q = 0; q < gv.G; ++q) ptr[q + 1] = ptr[q] + (ptr[q + 1] + 3) / 4 * 4;
-    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1), node(static_cast<size_t>(ptr.back()), 0);
+    for (int64_t q = 0; q < gv.G; ++q) ptr[q + 1] = ptr[q] + (ptr[q + 1] + 3) / 4;
+    std::vector<int64_t> fill(static_cast<size_t>(gv.G));
+    for (int64_t q = 0; q < gv.G; ++q) fill[q] = 4 * static_cast<int64_t>(ptr[q]);
+    std::vector<int32_t> node(4 * static_cast<size_t>(ptr.back()), 0);
     std::vector<double> w64(node.size(), 0.0);
     for (int i = 0; i < n; ++i)      // nodes in order within each list
         for (int cc = 0; cc < 8; ++cc) {
             const size_t e = 8 * static_cast<size_t>(i) + cc;
-            const int32_t slot = fill[static_cast<size_t>(row_of[static_cast<size_t>(gidx[e])])]++;
+            const int64_t slot = fill[static_cast<size_t>(row_of[static_cast<size_t>(gidx[e])])]++;
             node[slot] = i;
             w64[slot] = wts[e];
         }
     for (int64_t q = 0; q < gv.G; ++q)      // the padding gathers what the row gathers anyway
-        for (int32_t e = fill[q]; e < ptr[q + 1]; ++e) node[e] = node[ptr[q]];
+        for (int64_t e = fill[q]; e < 4 * static_cast<int64_t>(ptr[q + 1]); ++e) node[e] = node[4 * static_cast<int64_t>(ptr[q])];
     const size_t tb = f32 ? sizeof(float) : sizeof(double);
     rc = pc_alloc(c, &pc.rptr, ptr.size());
     if (!rc) rc = pc_alloc(c, &pc.rgrid, rgrid.size());

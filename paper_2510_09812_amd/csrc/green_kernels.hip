@@ -100,8 +100,8 @@ __global__ void __launch_bounds__(kThreads) k_pc_restrict(GreenView gv, int n, c
             }
     };
     if (t < gv.G) {
-        e0 = gv.rptr[t] / 4;
-        e1 = gv.rptr[t + 1] / 4;
+        e0 = gv.rptr[t];
+        e1 = gv.rptr[t + 1];
         g = gv.rgrid[t];
         entries(e0);
     }
