@@ -17,7 +17,8 @@ magnetostatics).  `value` is the fastest mixed-precision path of the
 workload's physics that stays within 1e-6 of the FP64 run on m and u.  Prints
 one JSON line, including the roofline of that path's dominant kernel (its
 launches timed by start and end events the HIP runtime records at each
-kernel's own execution, in extra untimed steps after the timed region) and
+kernel's own execution, or whole one-launch solves over their iterations, in
+extra untimed steps after the timed region) and
 the CPU oracle's throughput on a bounded sample of the same workload.
 """
 from __future__ import annotations
@@ -45,6 +46,10 @@ TRAFFIC = {
                 ["paper_2510_09812_amd/csrc/elem_kernels.hip", "paper_2510_09812_amd/csrc/device_common.h"]),
     "gs": ("profiles/traffic_gs_rows_cg_cube100.json",
            ["paper_2510_09812_amd/csrc/row_kernels.hip", "paper_2510_09812_amd/csrc/device_common.h"]),
+    # whole GS solves in one launch: bytes of the launches over their iterations
+    "gs_one_launch": ("profiles/traffic_resident_gs_cube100.json",
+                      ["paper_2510_09812_amd/csrc/resident_kernel.h", "paper_2510_09812_amd/csrc/resident.h",
+                       "paper_2510_09812_amd/csrc/device_common.h"]),
 }
 
 
@@ -95,6 +100,22 @@ def gs3_iteration_bytes(n_nodes: int, n_mag_tets: int, real_bytes: int = 4, jaco
     tetrahedra, FP64 coordinates, nine vector passes per component (as
     gs_iteration_bytes) and, with Jacobi preconditioning, the diagonal once."""
     return 16 * n_mag_tets + 24 * n_nodes + 3 * 9 * real_bytes * n_nodes + (real_bytes * n_nodes if jacobi else 0)
+
+
+def rows_iteration_bytes(n_nodes: int, n_tets: int, real_bytes: int, per_entry: int, diagonal: bool) -> int:
+    """What an iteration inside a one-launch solve streams, its vectors being on
+    the chip: per entry of the rows `per_entry` coefficients and a 16-bit
+    column, and the diagonal.  A closed mesh of V nodes and T tetrahedra has V + T
+    edges, each two entries (81.4 + 3.9 MB for the FP32 GS rows of the 1M-node
+    cube)."""
+    return 2 * (n_nodes + n_tets) * (per_entry * real_bytes + 2) + (real_bytes * n_nodes if diagonal else 0)
+
+
+def one_launch(n_nodes: int, mixed: bool, elastic: bool) -> bool:
+    """Whether the solves run whole in one launch: by rows per workgroup, one
+    workgroup per CU of 256."""
+    rows = max(64, -(-n_nodes // 256 // 64) * 64)
+    return rows <= (1024 if elastic else 4096 if mixed else 2048)
 
 
 def pcg_matvec_bytes(n_nodes: int, n_tets: int, real_bytes: int = 4) -> int:
@@ -507,15 +528,26 @@ def main() -> int:
     if pst and (pst["matvec_launches"] > 0 or pst["gs_matvec_launches"] > 0):
         if pst["gs_matvec_ms"] > pst["matvec_ms"]:
             launches, tot_ms = pst["gs_matvec_launches"], pst["gs_matvec_ms"]
-            mb = gs3_iteration_bytes(n, ne_mag, rb, jacobi=precond)
-            # in the mixed form the 1M-node solves run whole in one launch, timed over their iterations
-            kname = (f"k_resident<{tname},3>" if mixed else f"k_gs_rows_cg<{tname},3>") + (" (Jacobi)" if precond else "")
+            path = ("mixed" if mixed else "fp64") + ("+precond" if precond else "")
+            whole = one_launch(n, mixed, elastic=False)
             what = "GS CG iteration on three components"
-            traffic = traffic_from_profile("gs", ("mixed" if mixed else "fp64") + ("+precond" if precond else ""),
-                                           case.name)
+            if whole:
+                mb = rows_iteration_bytes(n, ne_mag, rb, 1, diagonal=True)
+                kname = f"k_resident<{tname},3>" + (" (Jacobi)" if precond else "")
+                traffic = traffic_from_profile("gs_one_launch", path, case.name)
+            else:
+                mb = gs3_iteration_bytes(n, ne_mag, rb, jacobi=precond)
+                kname = f"k_gs_rows_cg<{tname},3>" + (" (Jacobi)" if precond else "")
+                traffic = traffic_from_profile("gs", path, case.name)
         else:
             launches, tot_ms = pst["matvec_launches"], pst["matvec_ms"]
-            if precond:
+            whole = not precond and one_launch(n, mixed, elastic=True)
+            what = "elastic CG iteration"
+            if whole:
+                mb = rows_iteration_bytes(n, ne, rb, 6, diagonal=False)
+                kname = f"k_resident<{tname},3,blocks>"
+                traffic = None
+            elif precond:
                 mb = pcg_matvec_bytes(n, ne, rb)
                 kname = f"k_strip<{tname},3,3,ElasticPcgOp>"
                 traffic = traffic_from_profile("elastic", ("mixed" if mixed else "fp64") + "+precond", case.name)
@@ -523,15 +555,19 @@ def main() -> int:
                 mb = cg_iteration_bytes(n, ne, rb)
                 kname = f"k_strip<{tname},3,3,ElasticCgOp>"
                 traffic = traffic_from_profile("elastic", "mixed" if mixed else "fp64", case.name)
-            what = "elastic CG iteration launch"
         avg_s = tot_ms / launches * 1e-3
         achieved = mb / avg_s / 1e9
-        roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        # an iteration by launches is priced with the method's vector passes against HBM; inside a one-launch solve the
+        # rows stream from Infinity Cache and the chain of an exchange, not a rate, sets the time
+        roofline = {"bound": "latency" if whole else "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kname, "bytes_per_launch": mb,
                     "avg_launch_us": avg_s * 1e6, "launches": launches,
                     "share_of_timed_kernels": {"elastic_ms": pst["matvec_ms"], "gs3_iteration_ms": pst["gs_matvec_ms"]},
-                    "timing": f"kernel start/end events (hipExtLaunchKernelGGL) on every working {what} of "
-                              f"{args.profile_steps} untimed steps after the timed region"}
+                    "timing": (f"events around every one-launch solve of {args.profile_steps} untimed steps after the timed "
+                               f"region, refinements included, over their iterations ({what}); bytes and traffic likewise"
+                               if whole else
+                               f"kernel start/end events (hipExtLaunchKernelGGL) on every working launch ({what}) of "
+                               f"{args.profile_steps} untimed steps after the timed region")}
     mech_per_step = st["mech_iters"] / args.steps
     gs_per_step = st["gs_iters"] / args.steps
     mref = st["mech_refinements"] / args.steps

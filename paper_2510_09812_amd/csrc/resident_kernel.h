@@ -9,12 +9,15 @@
 // range of rows of the assembled operator; r, x and q of its rows stay in
 // registers, p of its rows and of their halo columns in LDS, and so do the
 // rows' coefficients where a thread has one row (beyond, they stream from L2
-// and Infinity Cache).  GS iteration on three components, launch-per-iteration
-// form (without the gaps between launches) against a whole solve here over its
-// iterations: 11.8 -> 5.8 us (729 nodes, FP64), 16.2 -> 6.8 us (97k nodes,
-// FP64), 20.6 -> 6.9 us (97k, FP32), 51 -> 35 us (970k, FP32, bound by the
-// rows' stream of 84 MB); a mixed solve also loses the host's turn in each
-// refinement.
+// and Infinity Cache).  An iteration by launches (with the gaps between them)
+// against one here, us, FP64 / FP32 inner:
+//   GS, three components: 729 nodes 13.4 -> 4.1 / -; 97k 19.3 -> 6.6 / 22.1 ->
+//   6.1; 358k 42 -> 18 / 30 -> 14; 970k - / 54 -> 29, where the rows' stream of
+//   85 MB from Infinity Cache would take 12 at that cache's copy rate;
+//   elastic: 729 nodes 20.2 -> 3.4 / 18.0 -> 3.2; 97k 28.7 -> 8.1 / 20.7 -> 5.4;
+//   149k 36 -> 20 / 26 -> 13; 250k 49 -> 29 / 32 -> 18;
+//   K^ms, three components: 250k 59 -> 12 / 41 -> 9; 970k - / 100 -> 24.
+// A mixed solve also loses the host's turn in each refinement.
 //
 // The halo keeps its own r and p: every workgroup applies the same alpha and
 // beta to the halo values it staged, so an iteration exchanges q alone, and q

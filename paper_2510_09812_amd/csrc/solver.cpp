@@ -327,7 +327,8 @@ namespace {
 // Rows per workgroup up to which K^mech runs in row form: 26 bytes of FP32
 // coefficients and column (50 in FP64) per entry, 14 entries per row, against
 // the strips' 16-bit connectivity.  At 262k nodes that is 95 MB an iteration
-// (184 MB in FP64), which Infinity Cache still holds; at 1M nodes it would be
+// (184 MB in FP64), which Infinity Cache still holds, and an iteration takes 18
+// us against 32 by launches (29 against 49 in FP64); at 1M nodes it would be
 // read from HBM in the time the matrix-free kernel takes (82 us).
 constexpr int kResElasticRows = 1024;
 
