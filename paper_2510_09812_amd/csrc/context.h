@@ -247,6 +247,7 @@ struct gspm_ctx {
     gspm::ResResult *h_res = nullptr;     // pinned (after h_step's sums): the running solve's outcome
     bool res_off = false;                 // a launch failed or ran out of time: launch-per-iteration from then on
     bool one_launch = true;               // gspm_set_solve_path
+    bool still[gspm::SK_COUNT] = {};      // the last one-launch solve of the kind took no iteration
     int64_t res_wait = gspm::kResWaitTicks;
     size_t lds_max = 0;
     int cus = 0;

@@ -196,6 +196,67 @@ CgResult cg_fp64(gspm_ctx *c, int nc, bool joint, double *x, double tol, int max
 
 constexpr const char *kBelowF32 = "the FP32 inner solve cannot reduce the residual: it is below the range of FP32";
 
+// The true residual r = b - A x in FP64, its test against tol |b| for every
+// scalar set, and x = 0 where b is zero; `all`: nothing is left to do (or,
+// with a status, the residual is not finite).
+struct OuterTest {
+    int status = GSPM_OK;
+    double rr[kMaxComp] = {0, 0, 0}, bb[kMaxComp] = {0, 0, 0};
+    bool conv[kMaxComp] = {true, true, true}, all = true;
+};
+
+template <class Resid>
+OuterTest outer_test(gspm_ctx *c, int nc, bool joint, double *x, double tol, SolveKind kind, Resid resid) {
+    hipStream_t s = c->stream;
+    const int ns = joint ? 1 : nc, n = c->n;
+    double *hs = c->h_mixed;   // pinned: the totals rr[ns] | bb[ns] of the residual
+    OuterTest t;
+    launch_zero_ring(c->cg, ns, 0, 1, 0, 0, s);
+    resid();
+    ShardSources src{};
+    for (int q = 0; q < ns; ++q) {
+        src.p[q] = c->cg.rr_at(q, 0);
+        src.p[ns + q] = c->cg.bb_at(q);
+    }
+    launch_totals_to_host(src, 2 * ns, hs, s);
+    t.status = hip_check(c, hipStreamSynchronize(s), "CG");
+    if (t.status) return t;
+    double worst = 0.0;
+    for (int q = 0; q < ns; ++q) {
+        t.rr[q] = hs[q];
+        t.bb[q] = hs[ns + q];
+        if (!std::isfinite(t.rr[q])) {
+            t.status = GSPM_E_NONFINITE;
+            c->err = "non-finite residual";
+            return t;
+        }
+        if (t.bb[q] == 0.0) {
+            for (int cc = 0; cc < nc; ++cc)
+                if ((joint ? 0 : cc) == q) launch_fill(x + static_cast<size_t>(cc) * n, n, 0.0, s);
+        }
+        t.conv[q] = t.bb[q] == 0.0 || t.rr[q] <= tol * tol * t.bb[q];
+        t.all &= t.conv[q];
+        if (t.bb[q] > 0.0) worst = std::max(worst, std::sqrt(std::max(t.rr[q], 0.0) / t.bb[q]));
+    }
+    if (t.all) c->last_res[kind] = worst;
+    return t;
+}
+
+// A mixed solve of a kind whose last solve took no iteration (a state at rest):
+// the start is tested by launches before a one-launch solve is made of it.  That
+// launch costs its way through the cooperative queue, and its residual runs
+// with one workgroup a CU: 10 us more than these launches at 729 nodes, 60 to
+// 70 at 970k (a step at rest 1.71 ms against 1.61).  Not in deterministic mode:
+// a resumed run does not know the last solve.
+template <class Resid>
+bool at_rest(gspm_ctx *c, int nc, bool joint, double *x, double tol, SolveKind kind, Resid resid, CgResult &res) {
+    if (!c->still[kind] || !c->one_launch || c->res_off || c->deterministic) return false;
+    const OuterTest t = outer_test(c, nc, joint, x, tol, kind, resid);
+    res = CgResult{};
+    res.status = t.status;
+    return t.status != GSPM_OK || t.all;
+}
+
 // Mixed form: FP64 iterative refinement around FP32 CG.  Each outer step
 // computes the true residual r = b - A x with the FP64 operator and stops
 // when ||r|| <= tol ||b|| for every component (the same criterion as the
@@ -213,46 +274,16 @@ CgResult cg_mixed(gspm_ctx *c, int nc, bool joint, double *x, double tol, int ma
     const size_t n3 = 3 * static_cast<size_t>(n);
     CgResult res;
     int total[kMaxComp] = {0, 0, 0};
-    double *hs = c->h_mixed;   // pinned: the totals rr[ns] | bb[ns] of the outer residual
     for (int outer = 0;; ++outer) {
-        launch_zero_ring(c->cg, ns, 0, 1, 0, 0, s);
         launch_zero_ring(c->cg_in, ns, 0, 1, 0, 0, s);   // slot 0 of an inner solve that may follow
-        resid();
-        ShardSources src{};
-        for (int q = 0; q < ns; ++q) {
-            src.p[q] = c->cg.rr_at(q, 0);
-            src.p[ns + q] = c->cg.bb_at(q);
-        }
-        launch_totals_to_host(src, 2 * ns, hs, s);
-        int rc = hip_check(c, hipStreamSynchronize(s), "CG");
-        if (rc) {
-            res.status = rc;
+        const OuterTest t = outer_test(c, nc, joint, x, tol, kind, resid);
+        if (t.status) {
+            res.status = t.status;
             return res;
         }
-        double rr[kMaxComp] = {0, 0, 0}, bb[kMaxComp] = {0, 0, 0};
-        bool conv[kMaxComp] = {true, true, true}, all = true;
-        for (int q = 0; q < ns; ++q) {
-            rr[q] = hs[q];
-            bb[q] = hs[ns + q];
-            if (!std::isfinite(rr[q])) {
-                res.status = GSPM_E_NONFINITE;
-                c->err = "non-finite residual";
-                return res;
-            }
-            if (bb[q] == 0.0) {
-                for (int cc = 0; cc < nc; ++cc)
-                    if ((joint ? 0 : cc) == q) launch_fill(x + static_cast<size_t>(cc) * n, n, 0.0, s);
-            }
-            conv[q] = bb[q] == 0.0 || rr[q] <= tol * tol * bb[q];
-            all &= conv[q];
-        }
-        if (all) {
-            double worst = 0.0;
-            for (int q = 0; q < ns; ++q)
-                if (bb[q] > 0.0) worst = std::max(worst, std::sqrt(std::max(rr[q], 0.0) / bb[q]));
-            c->last_res[kind] = worst;
-            break;
-        }
+        if (t.all) break;
+        const double *rr = t.rr, *bb = t.bb;
+        const bool *conv = t.conv;
         int used = 0;
         for (int q = 0; q < ns; ++q) used = std::max(used, total[q]);
         if (used >= maxit) {
@@ -567,6 +598,7 @@ bool cg_resident(gspm_ctx *c, ResArgs a, const ResComm &comm, int nc, bool blk, 
         c->err = "non-finite CG residual";
     } else {
         c->last_res[kind] = worst;
+        c->still[kind] = most == 0;
     }
     return true;
 }
@@ -654,7 +686,16 @@ CgResult cg_elastic(gspm_ctx *c, double *x, const double *b, double tol, int max
         return r;
     }
     const bool mixed = c->precision == GSPM_MIXED;
+    hipStream_t s = c->stream;
+    auto resid = [&]() {
+        launch_elastic_matvec<double>(c->mv, c->mat, MV_RESID, x, nullptr, b, c->d.r, nullptr, c->cg, 0, tol, s);
+    };
     if (operator_rows(c, true)) {
+        CgResult rest;
+        if (mixed && at_rest(c, 3, true, x, tol, kind, resid, rest)) {
+            c->prof_list = -1;
+            return rest;
+        }
         const OperatorRows &o = c->ops;
         ResArgs a{};
         a.ly = o.ly;
@@ -670,10 +711,6 @@ CgResult cg_elastic(gspm_ctx *c, double *x, const double *b, double tol, int max
         }
     }
     const size_t first_pair = prof_mark(c);
-    hipStream_t s = c->stream;
-    auto resid = [&]() {
-        launch_elastic_matvec<double>(c->mv, c->mat, MV_RESID, x, nullptr, b, c->d.r, nullptr, c->cg, 0, tol, s);
-    };
     // iteration k reads the buffers of iteration k-1 and writes those of k
     auto fused = [&](auto *R0, auto *R1, auto *P0, auto *P1, auto *Q0, auto *Q1, auto *xv, const CGScalars &cg,
                      double t) {
@@ -755,7 +792,12 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
     const bool mixed = c->precision == GSPM_MIXED;
     const double ls = c->mv.len_scale, scale = mixed ? 1.0 / (ls * ls * ls) : 1.0;
     const GsRowsView rw = mixed ? gs_rows(c, eps, 1.0, true) : r64;
-    {
+    auto resid = [&]() {
+        launch_gs_rows<double>(c->mv_rows, r64, nc, MV_RESID, x, nullptr, b, c->d.r, c->cg, s);
+    };
+    if (c->res_gs.nbr > 0) {
+        CgResult rest;
+        if (mixed && at_rest(c, nc, false, x, tol, kind, resid, rest)) return rest;
         ResArgs a{};
         a.ly = c->res_gs;
         a.a = rw.a;
@@ -769,9 +811,6 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
                   : cg_resident<double>(c, a, c->res_gs_comm, nc, false, x, b, tol, maxit, kind, r))
             return r;
     }
-    auto resid = [&]() {
-        launch_gs_rows<double>(c->mv_rows, r64, nc, MV_RESID, x, nullptr, b, c->d.r, c->cg, s);
-    };
     // iteration k reads the buffers of iteration k-1 and writes those of k
     auto fused = [&](const GsRowsView &rv, auto *R0, auto *R1, auto *P0, auto *P1, auto *Q0, auto *Q1, auto *xv,
                      const CGScalars &cg, double t) {
@@ -803,9 +842,14 @@ CgResult cg_gs_run(gspm_ctx *c, int nc, double eps, double *x, const double *b, 
 // solves' two-launch form with per-component scalars.
 CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int maxit, SolveKind kind) {
     hipStream_t s = c->stream;
+    auto resid = [&]() {
+        launch_ms_matvec<double>(c->mv, nc, MV_RESID, x, nullptr, b, c->d.r, nullptr, c->cg, 0, tol, s);
+    };
     if (operator_rows(c, false)) {
-        const OperatorRows &o = c->ops;
         const bool mixed = c->precision == GSPM_MIXED;
+        CgResult rest;
+        if (mixed && at_rest(c, nc, false, x, tol, kind, resid, rest)) return rest;
+        const OperatorRows &o = c->ops;
         const double ls = c->mv.len_scale;
         ResArgs a{};
         a.ly = o.ly;
@@ -818,9 +862,6 @@ CgResult cg_ms(gspm_ctx *c, int nc, double *x, const double *b, double tol, int 
                   : cg_resident<double>(c, a, o.comm, nc, false, x, b, tol, maxit, kind, r))
             return r;
     }
-    auto resid = [&]() {
-        launch_ms_matvec<double>(c->mv, nc, MV_RESID, x, nullptr, b, c->d.r, nullptr, c->cg, 0, tol, s);
-    };
     if (nc == 1) {
         auto fused = [&](auto *R0, auto *R1, auto *P0, auto *P1, auto *Q0, auto *Q1, auto *xv, const CGScalars &cg,
                          double t) {
