@@ -105,7 +105,7 @@ struct ResComm {
 // K^ms once.
 struct OperatorRows {
     bool tried = false, ready = false;    // the pattern
-    bool judged = false, k_fits = false, m_fits = false;   // whether solves on its layout fit the device
+    bool sized = false, k_fits = false, m_fits = false;   // whether solves on its layout fit the device
     bool k_ready = false, m_ready = false;
     bool looked = false, closed = false;  // K^mech: whether its blocks are symmetric (no free surface), else no rows
     ResLayout ly{};

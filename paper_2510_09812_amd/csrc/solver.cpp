@@ -422,7 +422,7 @@ bool build_pattern(gspm_ctx *c, bool elastic) {
     }
     o.k_fits = nbr <= kResElasticRows && resident_serves(c, ly, 3, true);
     o.m_fits = resident_serves(c, ly, 1, false);
-    o.judged = true;
+    o.sized = true;
     if (!(elastic ? o.k_fits : o.m_fits)) return false;
     int32_t *off = nullptr, *halo_ptr = nullptr, *halo_ids = nullptr, *slot = nullptr;
     uint16_t *col = nullptr;
@@ -462,10 +462,10 @@ bool build_rows(gspm_ctx *c, bool elastic) {
     auto &o = c->ops;
     if (!c->one_launch || c->res_off || rows_per_group(c) == 0) return false;
     if (elastic && rows_per_group(c) > kResElasticRows) return false;
-    if (o.judged && !(elastic ? o.k_fits : o.m_fits)) return false;
+    if (o.sized && !(elastic ? o.k_fits : o.m_fits)) return false;
     if (!o.tried) {
         o.ready = build_pattern(c, elastic);
-        if (!o.ready && o.judged && !(elastic ? o.k_fits : o.m_fits)) return false;   // the other operator may fit
+        if (!o.ready && o.sized && !(elastic ? o.k_fits : o.m_fits)) return false;   // the other operator may fit
         o.tried = true;
     }
     if (!o.ready) return false;

@@ -85,7 +85,7 @@ int main() {
         return 1;
     }
     long thrown = 0, tried = 0, wrong = 0;
-    auto judge = [&](const Result &r, bool may_throw) {
+    auto count = [&](const Result &r, bool may_throw) {
         ++tried;
         thrown += r.threw;
         if (r.threw ? !may_throw : !(r.ok && r.col == want.col && r.halo == want.halo && r.slot == want.slot)) ++wrong;
@@ -96,14 +96,14 @@ int main() {
         fail_at = k;
         run(n, tets, r);
         fail_at = -1;
-        judge(r, true);
+        count(r, true);
     }
     for (int most = 0; most < 2; ++most) {
         Result r;
         threads = 0;
         most_threads = most;
         run(n, tets, r);
-        judge(r, false);
+        count(r, false);
     }
     printf("%ld allocations, %ld runs, %ld threw, %ld wrong\n", total, tried, thrown, wrong);
     return wrong || thrown == 0 ? 1 : 0;

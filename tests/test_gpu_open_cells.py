@@ -88,7 +88,7 @@ def test_steps_match_the_oracle(kind):
     sim.close()
 
 
-def test_a_new_mesh_is_judged_anew():
+def test_a_new_mesh_is_looked_at_anew():
     """Closed, open, closed on one context: each upload decides for itself."""
     closed = w.small_cube(9, seed=49, L=8 * H, jitter=0.15)
     opened = _open_case("cavity", 9)

@@ -18,7 +18,7 @@ SANITIZERS = {"address": ["-fsanitize=address", "-fsanitize=undefined", "-fno-sa
 
 
 @pytest.fixture(scope="module", params=list(SANITIZERS))
-def checker(request, tmp_path_factory):
+def tool(request, tmp_path_factory):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
@@ -67,8 +67,8 @@ CASES = {
 
 
 @pytest.mark.parametrize("name", list(CASES))
-def test_layouts_match_brute_force_under_sanitizers(checker, name):
-    exe, d = checker
+def test_layouts_match_brute_force_under_sanitizers(tool, name):
+    exe, d = tool
     mesh, cus, reorder, rows = CASES[name]
     xyz, tets, tags, lo, hi = mesh()
     path = str(d / f"{name}.bin")
