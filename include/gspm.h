@@ -255,9 +255,9 @@ typedef enum {
 } gspm_solve_path;
 
 /* How the CG solves run.  In a one-launch solve the workgroups wait for each
- * other; one that waits longer than max_wait seconds (0: 5 s; another process
- * on the device can cause it) gives up, and the solve and the later ones on
- * the mesh run by launches.  Results keep their accuracy, iterations cost up to
+ * other; one that waits longer than max_wait seconds (0: 5 s) gives up, and the
+ * solve and the later ones on the mesh run by launches; so they do when such a
+ * launch is refused (a second process on the device).  Results keep their accuracy, iterations cost up to
  * four times as much.  set_solve_path(GSPM_PATH_AUTO) tries one launch again;
  * get_solve_path tells which way the next solve goes. */
 gspm_status gspm_set_solve_path(gspm_ctx *ctx, int32_t path, double max_wait);
